@@ -13,48 +13,58 @@
 // The solve is Gaussian elimination with partial pivoting (largest |pivot|,
 // the first row on ties) on the augmented matrix [K | C~] (TT, or the 2 x 2
 // block system for E/B) in the caller's workspace, then back substitution.
-// Panels are factorised in LDS by one work-group:
-//   * a panel of NB columns (8, or 4, 2 or 1 when its rows would not fit) by
-//     one wave, with no work-group barrier per column, when it has at most
-//     kWavePanelRows rows, else by every wave; the pivot's arg-max over a wave
-//     runs on DPP lane moves;
-//   * right of the panel, each column applies the panel's row exchanges and
-//     the unit-lower forward substitution U12 = L11^-1 A12;
-//   * the trailing block gets A22 -= L21 U12: lanes over 64 consecutive
-//     columns (U12 in registers), the waves split over (column chunk, row
-//     group) tasks, and each lane loads 8 rows before it stores any.
-// Small systems (m < kMultiMin) run all of it in one work-group
-// (master_solve_kernel).  Larger ones split the matrix into outer panels of
-// kOuterNB columns and spread the O(m^3) part over the chip:
-//   solve_assemble_kernel     [K | C~] into the workspace, one work-group per row;
-//   solve_panel_kernel        one work-group factorises the outer panel (rows
-//                             k0 .. m-1) in inner panels of NB columns as above,
-//                             keeping the row exchanges of the panel's earlier
-//                             columns (the L21 the update reads) in step;
-//   solve_swap_trsm_kernel    right of the outer panel, 64 columns per
-//                             work-group: the panel's row exchanges, composed
-//                             into one permutation of the touched rows and
-//                             applied through LDS, then U12 = L11^-1 A12;
-//   solve_update_kernel       A22 -= L21 U12 in 64 x 64 tiles (4 x 4 per
-//                             thread, the depth-64 operands staged in LDS);
-//   solve_back_kernel         back substitution (one work-group).
+// The workspace holds the matrix by columns (entry (r, c) at c m + r), so that
+// threads over rows, which the panels, the updates and the back substitution
+// all have, read consecutive addresses.
+//
+// Panels are factorised in registers (factor_rows): a thread owns whole rows of
+// the panel (RPT rows of NB columns, 64 doubles at most), so a column step
+// needs the pivot search and one broadcast row.  Per column, each wave finds its
+// largest entry (16-lane DPP maxima of the high words; the low words and the row
+// numbers only on ties), its owner leaves the row and 1/pivot in LDS, one
+// barrier, and every wave picks the winner among the waves' candidates; two LDS
+// buffers in turn need no second barrier.  Rows are not moved: a thread keeps
+// the position its row has after the exchanges.
+//
+// Small systems (m < kMultiMin) run in one work-group (master_solve_kernel),
+// with L21 and U12 staged in LDS and the trailing update on the matrix cores.
+// Larger ones split the matrix into outer panels of kOuterNB columns:
+//   solve_assemble_kernel     [K | C~] into the workspace, by columns;
+//   solve_panel_kernel        one work-group factorises NB columns (32 while the
+//                             panel has at most 1024 rows, 16, 8, 4, 2 for taller
+//                             ones) and applies their exchanges and U12 to the
+//                             outer panel's other columns; a panel of fewer than
+//                             kOuterNB columns is followed by an update of the
+//                             outer panel's later columns;
+//   solve_swap_trsm_kernel    right of the outer panel, one thread per column:
+//                             the panel's row exchanges, composed into one
+//                             permutation of the touched rows, then
+//                             U12 = L11^-1 A12;
+//   solve_update_kernel       A22 -= L21 U12 in 64 x 64 tiles on the float64
+//                             matrix cores (v_mfma_f64_16x16x4: each entry is a
+//                             chain of fused multiply-adds in column order);
+//   solve_back_block_kernel,  back substitution: one work-group solves a block of
+//   solve_back_above_kernel   kBackRows rows, then every row above it is updated.
 // The panel's pivots travel from the panel kernel to the swap kernel in the
 // first kOuterNB entries of x, and x[kOuterNB] is a singular flag that every
-// later kernel reads first; back substitution overwrites all of x last.
-// Back substitution: the right-hand sides (columns m .. of the augmented
-// matrix) in blocks of kBackBlock rows from the bottom, a chunk of them held in
-// LDS: one wave per right-hand side solves the diagonal block (lanes over its
-// rows), then every thread updates rows above from U read straight from memory.
+// later kernel reads first; the last swap kernel copies it to the workspace's
+// entry (m - 1, 0), an entry of L that is no longer read, for the back
+// substitution, which overwrites x.
 // A zero pivot (a singular system) gives NaN in every output.
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "couple_internal.hpp"
 
 namespace couple {
 namespace {
 
-constexpr int kSolveThreads = 1024;
+constexpr int kSolveThreads = 512;
 constexpr int kSolveWaves = kSolveThreads / kWave;
+constexpr int kTallThreads = 1024;           // the panel kernel for more than 16 x kSolveThreads rows
+constexpr int kMostWaves = kTallThreads / kWave;
+typedef double d4v __attribute__((ext_vector_type(4)));
 
 struct BinSpecArgs {
     const double* cl;            // [n_spec][cl_stride]
@@ -81,117 +91,11 @@ __global__ void __launch_bounds__(256) bin_spectra_kernel(BinSpecArgs a) {
 struct SolveArgs {
     const double* K;             // TT: [n][n]; E/B: [3][n][n] in the order EE, BB, EB
     const double* rhs;           // [n_rhs][m]
-    double* work;                // [m][m + n_rhs]
+    double* work;                // [m + n_rhs][m]: the augmented matrix by columns
     double* x;                   // [n_rhs][m]
     int n, m, n_rhs, pol;
 };
 
-// One step of the arg-max: the pair of the lane that DPP control Ctrl names
-// (a row shift or a row broadcast; rows outside RowMask and lanes with no
-// source keep their own pair) replaces this lane's pair if it is larger.
-template <int Ctrl, int RowMask>
-__device__ inline void argmax_dpp_step(double& v, int& idx) {
-    const long long b = __double_as_longlong(v);
-    const int lo = (int)(b & 0xffffffff), hi = (int)(b >> 32);
-    const int olo = __builtin_amdgcn_update_dpp(lo, lo, Ctrl, RowMask, 0xf, false);
-    const int ohi = __builtin_amdgcn_update_dpp(hi, hi, Ctrl, RowMask, 0xf, false);
-    const int oi = __builtin_amdgcn_update_dpp(idx, idx, Ctrl, RowMask, 0xf, false);
-    const double ov = __longlong_as_double(((long long)ohi << 32) | (unsigned int)olo);
-    if (ov > v || (ov == v && oi < idx)) {
-        v = ov;
-        idx = oi;
-    }
-}
-
-// The value of lane i (the same i in every lane) in every lane, from registers.
-__device__ inline double lane_value(double v, int i) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), i);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Largest (|v|, first row on ties) over the 64 lanes of a wave (all active),
-// returned in every lane.  Shifts by 1, 2, 4, 8 within each row of 16 lanes
-// leave each row's result in its lane 15; broadcasting lane 15 into the next
-// row and lane 31 into rows 2 and 3 leaves the wave's result in lane 63.
-__device__ inline void wave_argmax(double& v, int& idx) {
-    argmax_dpp_step<0x111, 0xf>(v, idx);    // row_shr:1
-    argmax_dpp_step<0x112, 0xf>(v, idx);    // row_shr:2
-    argmax_dpp_step<0x114, 0xf>(v, idx);    // row_shr:4
-    argmax_dpp_step<0x118, 0xf>(v, idx);    // row_shr:8
-    argmax_dpp_step<0x142, 0xa>(v, idx);    // row_bcast:15 into rows 1 and 3
-    argmax_dpp_step<0x143, 0xc>(v, idx);    // row_bcast:31 into rows 2 and 3
-    v = lane_value(v, kWave - 1);
-    idx = __builtin_amdgcn_readlane(idx, kWave - 1);
-}
-
-// Panel of NB columns in LDS: rows k0 .. m-1 (at most kPanelDoubles / NB).
-constexpr int kPanelDoubles = 16384;
-constexpr int kRowBatch = 8;      // rows of the trailing update loaded before any is stored
-constexpr int kWavePanelRows = 512;  // panels up to this many rows are factorised by one wave
-constexpr int kBackBlock = 64;    // rows per diagonal block of the back substitution
-
-// The work-group's LDS for factorising one panel.
-template <int NB>
-struct PanelLds {
-    double panel[kPanelDoubles];     // [row - k0][NB]
-    int perm[NB];                    // row exchanges of the panel (panel rows)
-    int sing;                        // the panel met a zero pivot
-    double cv[kSolveWaves];          // per-wave pivot candidates (tall panels)
-    int ci[kSolveWaves];
-    double pv;                       // chosen pivot magnitude and panel row
-    int pi;
-    int trow[2 * NB];                // rows the exchanges touch (panel-relative): the panel's top first
-    int tsrc[2 * NB];                // the row whose old values land in trow[i]
-    int tn;
-};
-
-// Compose the panel's exchanges (row j <-> perm[j], in order) into one
-// permutation of the rows they touch: after all of them, row trow[i] holds
-// what row tsrc[i] held before.  One thread; at most 2 NB rows.
-template <int NB>
-__device__ inline void compose_exchanges(PanelLds<NB>& L, int nb) {
-    int n = nb;
-    for (int j = 0; j < nb; ++j) L.trow[j] = L.tsrc[j] = j;
-    for (int j = 0; j < nb; ++j) {
-        const int p = L.perm[j];
-        if (p == j) continue;
-        int ip = -1;
-        for (int i = 0; i < n; ++i)
-            if (L.trow[i] == p) ip = i;
-        if (ip < 0) {
-            ip = n++;
-            L.trow[ip] = L.tsrc[ip] = p;
-        }
-        const int tmp = L.tsrc[j];
-        L.tsrc[j] = L.tsrc[ip];
-        L.tsrc[ip] = tmp;
-    }
-    L.tn = n;
-}
-
-// Rows k0 .. k0+mr-1, columns k0 .. k0+nb-1 of A into L.panel (columns nb ..
-// NB-1 zero).  Each thread issues kLoadBatch loads before it stores any.
-constexpr int kLoadBatch = 8;
-template <int NB>
-__device__ inline void load_panel(PanelLds<NB>& L, const double* A, long long ld, int k0, int mr, int nb) {
-    const int total = mr * NB;
-    for (int e0 = threadIdx.x; e0 < total; e0 += kSolveThreads * kLoadBatch) {
-        double v[kLoadBatch];
-#pragma unroll
-        for (int q = 0; q < kLoadBatch; ++q) {
-            const int e = e0 + q * kSolveThreads;
-            const int r = e / NB, j = e - r * NB;
-            v[q] = (e < total && j < nb) ? A[(k0 + r) * ld + k0 + j] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < kLoadBatch; ++q) {
-            const int e = e0 + q * kSolveThreads;
-            if (e < total) L.panel[e] = v[q];
-        }
-    }
-}
 
 // Entry (r, c) of the augmented matrix [K | C~]: TT, or [EE EB; EB BB] for E/B.
 __device__ inline double assembled(const SolveArgs& a, int r, int c) {
@@ -202,373 +106,717 @@ __device__ inline double assembled(const SolveArgs& a, int r, int c) {
     return a.K[((long long)blk * n + (r - br * n)) * n + (c - bc * n)];
 }
 
-// Factorise the mr x nb panel in L.panel with partial pivoting: multipliers
-// below the diagonal, U11 on and above it, the exchanges in L.perm.  Called by
-// every thread of the work-group; returns true (in every thread) on a zero or
-// NaN pivot column.
+// The value of lane i (the same i in every lane) in every lane, from registers.
+__device__ inline double lane_value(double v, int i) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), i);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The value of lane i of each row of 16 lanes, in every lane of the row
+// (row_newbcast; i a constant once the caller's loop is unrolled).
+template <int I>
+__device__ __forceinline__ double row16_lane(double v) {
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + I, 0xf, 0xf, true);
+}
+__device__ __forceinline__ double row16_bcast(double v, int i) {
+    switch (i & 15) {
+    case 0: return row16_lane<0>(v);
+    case 1: return row16_lane<1>(v);
+    case 2: return row16_lane<2>(v);
+    case 3: return row16_lane<3>(v);
+    case 4: return row16_lane<4>(v);
+    case 5: return row16_lane<5>(v);
+    case 6: return row16_lane<6>(v);
+    case 7: return row16_lane<7>(v);
+    case 8: return row16_lane<8>(v);
+    case 9: return row16_lane<9>(v);
+    case 10: return row16_lane<10>(v);
+    case 11: return row16_lane<11>(v);
+    case 12: return row16_lane<12>(v);
+    case 13: return row16_lane<13>(v);
+    case 14: return row16_lane<14>(v);
+    default: return row16_lane<15>(v);
+    }
+}
+
+// Largest of v over each row of 16 lanes (all lanes active), by rotations of 8, 4, 2 and 1.
+__device__ inline unsigned row16_max(unsigned v) {
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, true));   // row_ror:8
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xf, 0xf, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xf, 0xf, true));
+    return v;
+}
+
+// Largest of v over the wave: over each row of 16 lanes, then the four rows' results on the scalar unit.
+__device__ inline unsigned wave_max(unsigned v) {
+    v = row16_max(v);
+    const unsigned a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+    const unsigned c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+    return max(max(a, b), max(c, d));
+}
+
+// Whether the high word of a magnitude has an exponent in [-1000, 1000]: its
+// reciprocal and the correction step of a quotient are then finite and normal.
+__device__ inline bool plain_exponent(unsigned hi) { return (hi >> 20) - 23u <= 2000u; }
+
+// LDS of factor_rows.
 template <int NB>
-__device__ bool factor_panel(PanelLds<NB>& L, int mr, int nb) {
-    const int t = threadIdx.x;
-    const int lane = t % kWave, wave = t / kWave;
-    double* s_panel = L.panel;
-    if (mr <= kWavePanelRows) {
-        // short panel: one wave, no work-group barrier per column
-        if (wave == 0) {
-            bool sing = false;
-            for (int j = 0; j < nb; ++j) {
-                double best = -1.0;
-                int bi = mr;
-                for (int r = j + lane; r < mr; r += kWave) {
-                    const double v = fabs(s_panel[r * NB + j]);
-                    if (v > best) {
-                        best = v;
-                        bi = r;
+struct PivotLds {
+    double blk[NB][NB + 2];       // row j of the factorised top block (L11 and U11), in the register order of step j
+    int4 key[2][kMostWaves];      // each wave's candidate: high and low word of |pivot|, row position
+    int piv[NB];                  // row exchanged with row j at step j (panel rows)
+    int sing;                     // the panel met a zero pivot
+};
+
+// The rows of a panel that a thread holds: row threadIdx.x + q stride in a[q].
+// A row leaves when it becomes a pivot (step = its column; its live columns go
+// to PivotLds::blk and are 0 here from then on); step is -1 before that, and NB
+// where there is no row.  pos is the position of row q = 0, which only an
+// exchange with one of the panel's first NB rows changes.  Other rows stay
+// where they are until they leave.
+template <int NB, int RPT>
+struct PanelRows {
+    double a[RPT][NB];
+    int step[RPT];
+    int stride, pos;
+    __device__ __forceinline__ int row(int q) const { return (int)threadIdx.x + q * stride; }
+    __device__ __forceinline__ int position(int q) const { return q == 0 ? pos : row(q); }
+};
+
+// Column jj of factor_rows, J of its block of GB in the register window, whose
+// first live entries are the block's columns and those after it.
+template <int NB, int RPT, int GB, int J>
+__device__ __forceinline__ void factor_column(PanelRows<NB, RPT>& R, int jj, int live, int waves, PivotLds<NB>& S) {
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // the wave's largest entry (high words, low words only on ties), its lane w
+    double mx = 0.0;
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) mx = fmax(mx, fabs(R.a[q][J]));
+    const long long bits = __double_as_longlong(mx);
+    const unsigned hi = (unsigned)(bits >> 32), lo = (unsigned)bits;
+    unsigned kh = wave_max(hi);
+    bool in = hi == kh;
+    unsigned long long cand = __ballot(in);
+    if (cand & (cand - 1)) {
+        const unsigned ml = wave_max(in ? lo : 0u);
+        in = in && lo == ml;
+        cand = __ballot(in);
+        if (cand & (cand - 1)) {
+            int bp = 0x7fffffff;                      // the first row on ties
+#pragma unroll
+            for (int q = 0; q < RPT; ++q)
+                if (fabs(R.a[q][J]) == mx && R.step[q] < 0) bp = min(bp, R.position(q));
+            const unsigned key = 0x7fffffffu - (unsigned)bp, best = wave_max(in ? key : 0u);
+            cand = __ballot(in && key == best);
+        }
+    }
+    const int w = __ffsll((long long)cand) - 1;
+    unsigned kl = __builtin_amdgcn_readlane((int)lo, w);
+    // which of the lane's rows, and its position
+    int wq = 0, p = 0x7fffffff;
+    if (RPT == 1) {
+        p = __builtin_amdgcn_readlane(R.pos, w);
+    } else {
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) {
+            const bool is = __ballot(fabs(R.a[q][J]) == mx && R.step[q] < 0) >> w & 1;
+            const int pq = q == 0 ? __builtin_amdgcn_readlane(R.pos, w) : wave * kWave + w + q * R.stride;
+            if (is && pq < p) {
+                p = pq;
+                wq = q;
+            }
+        }
+    }
+    bool mine = true;
+    if (waves > 1) {
+        constexpr int buf = J & 1;
+        if (lane == 0) S.key[buf][wave] = make_int4((int)kh, (int)kl, p, 0);
+        __syncthreads();
+        const int4 k = S.key[buf][lane < waves ? lane : 0];
+        // the candidates' largest (at most 16: one row of lanes; copies of the first fill it up)
+        const unsigned h = row16_max((unsigned)k.x);
+        const unsigned mh = __builtin_amdgcn_readfirstlane((int)h);
+        bool on = lane < waves && (unsigned)k.x == mh;
+        unsigned long long c = __ballot(on);
+        if (c & (c - 1)) {
+            const unsigned ml = __builtin_amdgcn_readfirstlane((int)row16_max(on ? (unsigned)k.y : 0u));
+            on = on && (unsigned)k.y == ml;
+            c = __ballot(on);
+            if (c & (c - 1)) {
+                const unsigned key = 0x7fffffffu - (unsigned)k.z;
+                const unsigned best = __builtin_amdgcn_readfirstlane((int)row16_max(on ? key : 0u));
+                c = __ballot(on && key == best);
+            }
+        }
+        const int cw = __ffsll((long long)c) - 1;
+        mine = cw == wave;
+        kh = mh;
+        kl = __builtin_amdgcn_readlane(k.y, cw);
+        p = __builtin_amdgcn_readlane(k.z, cw);
+    }
+    // the pivot row leaves its registers
+    if (mine) {
+        if (lane == w) {
+            double* r = S.blk[jj];
+#pragma unroll
+            for (int q = 0; q < RPT; ++q)
+                if (q == wq) {
+#pragma unroll
+                    for (int g = 0; g < NB; g += GB) {
+                        if (g > 0 && g >= live) continue;
+#pragma unroll
+                        for (int c = g; c < g + GB; ++c) {
+                            r[c] = R.a[q][c];
+                            R.a[q][c] = 0.0;
+                        }
                     }
+                    R.step[q] = jj;
+                    // the branches stay apart: merged, they would index a in scratch
+                    if (RPT > 1) asm volatile("; row %0" ::"s"(q));
                 }
-                wave_argmax(best, bi);
-                if (!(best > 0.0)) {         // zero (or NaN) pivot column: the system is singular
-                    sing = true;
-                    break;
-                }
-                bi = min(max(bi, j), mr - 1);    // a candidate row of this column
-                if (lane < NB && bi != j) {
-                    const double x = s_panel[j * NB + lane];
-                    s_panel[j * NB + lane] = s_panel[bi * NB + lane];
-                    s_panel[bi * NB + lane] = x;
-                }
-                if (lane == 0) L.perm[j] = bi;
-                // the exchanged rows are read by other lanes of this wave
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                // multipliers of column j and the rank-1 update of the panel's later columns
-                const double piv = s_panel[j * NB + j];
-                for (int r = j + 1 + lane; r < mr; r += kWave) {
-                    const double l = s_panel[r * NB + j] / piv;
-                    s_panel[r * NB + j] = l;
-#pragma unroll
-                    for (int cc = 0; cc < NB; ++cc)
-                        if (cc > j && cc < nb) s_panel[r * NB + cc] = __builtin_fma(-l, s_panel[j * NB + cc], s_panel[r * NB + cc]);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
-            if (lane == 0) L.sing = sing ? 1 : 0;
+            S.piv[jj] = p;
+            if ((kh | kl) == 0) S.sing = 1;
         }
-        __syncthreads();
-        return L.sing != 0;
     }
-    // tall panel: every wave scans rows; four work-group barriers per column
-    for (int j = 0; j < nb; ++j) {
-        double best = -1.0;
-        int bi = mr;
-        for (int r = j + t; r < mr; r += kSolveThreads) {
-            const double v = fabs(s_panel[r * NB + j]);
-            if (v > best) {
-                best = v;
-                bi = r;
-            }
-        }
-        wave_argmax(best, bi);
-        if (lane == 0) {
-            L.cv[wave] = best;
-            L.ci[wave] = bi;
-        }
-        __syncthreads();
-        if (wave == 0) {
-            double v = lane < kSolveWaves ? L.cv[lane] : -1.0;
-            int idx = lane < kSolveWaves ? L.ci[lane] : mr;
-            wave_argmax(v, idx);
-            if (lane == 0) {
-                L.pv = v;
-                L.pi = idx;
-            }
-        }
-        __syncthreads();
-        if (!(L.pv > 0.0)) return true;      // zero (or NaN) pivot column: the system is singular
-        const int p = min(max(L.pi, j), mr - 1);    // a candidate row of this column
-        if (t < NB && p != j) {
-            const double x = s_panel[j * NB + t];
-            s_panel[j * NB + t] = s_panel[p * NB + t];
-            s_panel[p * NB + t] = x;
-        }
-        if (t == 0) L.perm[j] = p;
-        __syncthreads();
-        // multipliers of column j and the rank-1 update of the panel's later columns
-        const double piv = s_panel[j * NB + j];
-        for (int r = j + 1 + t; r < mr; r += kSolveThreads) {
-            const double l = s_panel[r * NB + j] / piv;
-            s_panel[r * NB + j] = l;
+    R.pos = R.pos == jj ? p : R.pos;
+    // a / |pivot|: from the reciprocal with one correction step, or by division
+    const double apv = __longlong_as_double(((long long)kh << 32) | kl);
+    const double inv = 1.0 / apv;
+    double l[RPT];
 #pragma unroll
-            for (int cc = 0; cc < NB; ++cc)
-                if (cc > j && cc < nb) s_panel[r * NB + cc] = __builtin_fma(-l, s_panel[j * NB + cc], s_panel[r * NB + cc]);
-        }
-        __syncthreads();
+    for (int q = 0; q < RPT; ++q) {
+        l[q] = R.a[q][J] * inv;
+        l[q] = __builtin_fma(__builtin_fma(-l[q], apv, R.a[q][J]), inv, l[q]);
     }
-    return false;
+    if (!plain_exponent(kh)) {
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) l[q] = R.a[q][J] / apv;
+    }
+    if (waves > 1) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    const double* r = S.blk[jj];
+    const double r0 = r[lane % (NB < 16 ? NB : 16)];
+    const double r1 = NB > 16 ? r[16 + lane % 16] : 0.0;
+    const double pv = row16_bcast(r0, J);
+    const long long sign = __double_as_longlong(pv) & (1LL << 63);
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+        R.a[q][J] = __longlong_as_double(__double_as_longlong(l[q]) ^ sign);
+        l[q] = -R.a[q][J];
+    }
+    // the columns after jj, block by block (rows that left hold zeros)
+#pragma unroll
+    for (int g = 0; g < NB; g += GB) {
+        if (g > 0 && g >= live) continue;
+        double u[GB];
+#pragma unroll
+        for (int c = g; c < g + GB; ++c)
+            if (c > J) u[c - g] = row16_bcast(c < 16 ? r0 : r1, c);
+#pragma unroll
+        for (int c = g; c < g + GB; ++c)
+#pragma unroll
+            for (int q = 0; q < RPT; ++q)
+                if (c > J) R.a[q][c] = __builtin_fma(l[q], u[c - g], R.a[q][c]);
+    }
 }
 
-// Column c right of the panel at k0 (nb columns, factorised in s_panel):
-// the panel's row exchanges, then U12 = L11^-1 A12 in place.
-template <int NB>
-__device__ inline void exchange_and_solve_column(double* A, long long ld, int k0, int nb, const PanelLds<NB>& L,
-                                                 long long c, bool solve) {
-    for (int j = 0; j < nb; ++j) {
-        const int p = L.perm[j];
-        if (p != j) {
-            const double x = A[(k0 + j) * ld + c];
-            A[(k0 + j) * ld + c] = A[(k0 + p) * ld + c];
-            A[(k0 + p) * ld + c] = x;
-        }
+template <int NB, int RPT, int GB, int J>
+__device__ __forceinline__ void factor_block(PanelRows<NB, RPT>& R, int j0, int nb, int waves, PivotLds<NB>& S) {
+    if constexpr (J < GB) {
+        if (j0 + J < nb) factor_column<NB, RPT, GB, J>(R, j0 + J, NB - j0, waves, S);
+        factor_block<NB, RPT, GB, J + 1>(R, j0, nb, waves, S);
     }
-    if (!solve) return;
-    double u[NB];
+}
+
+// Factorise a panel of nb <= NB columns held in registers by the first `waves`
+// waves, with partial pivoting.  Afterwards the rows that have not left hold
+// their multipliers, S.blk the top block (entry (j, c) by top_entry) and S.piv
+// the exchanges.  Every thread of the work-group calls this (waves beyond
+// `waves` only keep the barriers company).  S.sing is set if a pivot column was
+// zero or NaN: the caller checks it first, since positions and exchanges (never
+// used as an address in here) then hold nothing of use.
+// Columns run in blocks of 8 through one copy of the code, the registers rotated
+// by a block after each (a copy per column would be 90 KB for 32 columns, more
+// than the instruction cache holds).  What bounds it: the dependent chain of a
+// column (search, two barriers with an LDS exchange each, then the update).
+template <int NB, int RPT>
+__device__ __forceinline__ void factor_rows(PanelRows<NB, RPT>& R, int nb, int waves, PivotLds<NB>& S) {
+    constexpr int GB = NB < 8 ? NB : 8;
+    if ((int)(threadIdx.x / kWave) >= waves) {
+        if (waves > 1)
+            for (int j = 0; j < 2 * nb; ++j) __syncthreads();
+        return;
+    }
+#pragma unroll 1
+    for (int j0 = 0; j0 < NB; j0 += GB) {
+        factor_block<NB, RPT, GB, 0>(R, j0, nb, waves, S);
+        if (NB > GB) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        if (j < nb) {
-            double v = A[(k0 + j) * ld + c];
+            for (int q = 0; q < RPT; ++q) {
+                double t[GB];
 #pragma unroll
-            for (int i = 0; i < NB; ++i)
-                if (i < j) v = __builtin_fma(-L.panel[j * NB + i], u[i], v);
-            u[j] = v;
-            A[(k0 + j) * ld + c] = v;
+                for (int c = 0; c < GB; ++c) t[c] = R.a[q][c];
+#pragma unroll
+                for (int c = 0; c < NB - GB; ++c) R.a[q][c] = R.a[q][c + GB];
+#pragma unroll
+                for (int c = 0; c < GB; ++c) R.a[q][NB - GB + c] = t[c];
+            }
         }
     }
 }
 
-// As exchange_and_solve_column with the exchanges composed (compose_exchanges):
-// every touched row is loaded before any is stored, so the loads overlap.
-template <int NB>
-__device__ inline void permute_and_solve_column(double* A, long long ld, int k0, int nb, const PanelLds<NB>& L,
-                                                long long c, bool solve) {
-    const int n = L.tn;
-    double v[2 * NB];
+// The factorised panel: put(r, c, v) for every entry that it holds, row
+// positions r and columns c < nb.  The rows that have not left and the finished
+// columns of the pivot rows (L11 left of the block of GB they left in) come
+// from the registers, the rest of the top block from blk (at step j its columns
+// had been rotated by whole blocks).
+template <int NB, int RPT, class Put>
+__device__ __forceinline__ void put_rows(const PanelRows<NB, RPT>& R, const PivotLds<NB>& S, int nb, Put put) {
+    constexpr int GB = NB < 8 ? NB : 8;
 #pragma unroll
-    for (int i = 0; i < 2 * NB; ++i)
-        if (i < n) v[i] = A[(k0 + L.tsrc[i]) * ld + c];
+    for (int q = 0; q < RPT; ++q) {
+        if (R.step[q] < 0) {
+            const int r = R.position(q);
+#pragma unroll
+            for (int c = 0; c < NB; ++c)
+                if (c < nb) put(r, c, R.a[q][c]);
+        } else if (NB > GB && R.step[q] >= GB && R.step[q] < NB) {
+#pragma unroll
+            for (int c = 0; c < NB - GB; ++c)
+                if (c < R.step[q] / GB * GB) put(R.step[q], c, R.a[q][c]);
+        }
+    }
+    for (int e = threadIdx.x; e < NB * NB; e += blockDim.x) {
+        const int j = e % NB, c = e / NB;
+        if (j < nb && c < nb && c >= j / GB * GB) put(j, c, S.blk[j][c - j / GB * GB]);
+    }
+}
+
+// Panel rows (mr rows from row k0 on, columns k0 .. k0 + nb - 1) into the
+// registers of the first `waves` waves; columns nb .. NB - 1 zero.
+template <int NB, int RPT>
+__device__ __forceinline__ void load_rows(PanelRows<NB, RPT>& R, const double* A, long long m, int k0, int mr, int nb,
+                                          int waves) {
+    R.stride = waves * kWave;
+    R.pos = threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+        const bool in = R.row(q) < mr && (int)threadIdx.x < R.stride;
+        const double* Ar = A + k0 * m + k0 + (in ? R.row(q) : 0);
+        R.step[q] = in ? -1 : NB;
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+            const double v = Ar[min(c, nb - 1) * m];
+            R.a[q][c] = (in && c < nb) ? v : 0.0;
+        }
+    }
+}
+
+// The panel's exchanges for its other columns: src[i] = the row whose old values
+// land in position i < nb, dst[i] = the position that old row i moves down to
+// (-1 if it stays among the first nb); moved (cleared a barrier earlier) where
+// any row moved.  One wave composes them from S.piv, lane i holding row i.
+template <int NB>
+__device__ inline void compose_moves(const PivotLds<NB>& S, int nb, int* src, int* dst, int* moved) {
+    static_assert(NB <= 32, "two rows per lane pair");
+    if (threadIdx.x >= kWave) return;
+    const int l = threadIdx.x;
+    // lanes 0 .. nb - 1: positions 0 .. nb - 1; lanes from nb on: positions below, as they are met
+    int at = l < nb ? l : -1, from = at;      // position, and the row it holds
+    int n = nb;
+    bool any = false;
+    const int piv = l < nb ? S.piv[l] : 0;
+    for (int j = 0; j < nb; ++j) {
+        const int p = __builtin_amdgcn_readlane(piv, j);
+        if (p == j) continue;
+        any = true;
+        unsigned long long h = __ballot(at == p);
+        if (!h) {
+            if (l == n) at = from = p;
+            h = 1ull << n++;
+        }
+        const int ip = __ffsll((long long)h) - 1;
+        const int fj = __builtin_amdgcn_readlane(from, j), fp = __builtin_amdgcn_readlane(from, ip);
+        if (l == j) from = fp;
+        if (l == ip) from = fj;
+    }
+    if (l < nb) {
+        src[l] = from;
+        dst[l] = -1;
+    }
+    if (any && l == 0) *moved = 1;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (l >= nb && l < n && from < nb) dst[from] = at;
+}
+
+// Column Ac of the matrix (from the panel's first row on): the panel's
+// exchanges, then with `solve` U12 = L11^-1 A12, L11 read as lp[i ls + j] (row
+// j, column i) times sign.  Every touched row is loaded before any is stored;
+// u returns the first nb rows (rows nb .. NB - 1 hold nothing of use).
+template <int NB>
+__device__ inline void move_and_solve(double* Ac, int nb, bool moved, const int* src, const int* dst, const double* lp,
+                                      int ls, double sign, bool solve, double (&u)[NB]) {
+    if (moved) {
+        double d[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            u[i] = Ac[src[min(i, nb - 1)]];
+            d[i] = Ac[min(i, nb - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (i < nb && dst[i] >= 0) Ac[dst[i]] = d[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) u[i] = Ac[min(i, nb - 1)];
+    }
     if (solve) {
+        int ofs = 0;
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            if (j < nb) {
+        for (int i = 0; i < NB; ++i) {
+            asm volatile("" : "+v"(ofs), "+v"(u[i]));   // a column of L11 is read when its turn comes, not before
 #pragma unroll
-                for (int i = 0; i < NB; ++i)
-                    if (i < j) v[j] = __builtin_fma(-L.panel[j * NB + i], v[i], v[j]);
-            }
+            for (int j = i + 1; j < NB; ++j) u[j] = __builtin_fma(sign * lp[ofs + i * ls + j], u[i], u[j]);
         }
     }
 #pragma unroll
-    for (int i = 0; i < 2 * NB; ++i)
-        if (i < n && (i < nb || L.trow[i] != L.tsrc[i])) A[(k0 + L.trow[i]) * ld + c] = v[i];
+    for (int i = 0; i < NB; ++i)
+        if (i < nb) Ac[i] = u[i];
 }
 
-// A[r][c] -= L21[r] U12[c] for rows k0+nb .. m-1 and columns c0 .. ce-1
-// (c0 = k0 + nb), L21 in s_panel.  Lanes go over lpr consecutive columns,
-// lpr the narrowest power of two (8 .. 64) that covers them, so a wave works
-// on 64 / lpr row sets at once; the waves take (column chunk, row group)
-// tasks, and each lane loads RB rows before it stores any.
-template <int NB, int RB>
-__device__ inline void panel_trailing_update(double* A, long long ld, int m, int k0, int nb, int ce,
-                                             const PanelLds<NB>& L) {
-    const int t = threadIdx.x;
-    const int lane = t % kWave, wave = t / kWave;
-    const int c0 = k0 + nb, w = ce - c0;
-    int lpr = kWave;
-    while (lpr > 8 && lpr / 2 >= w) lpr /= 2;
-    const int sets = kWave / lpr, sub = lane / lpr, cl = lane % lpr;
-    const int nchunk = (w + lpr - 1) / lpr;
-    const int groups = max(1, kSolveWaves / nchunk);
-    for (int task = wave; task < nchunk * groups; task += kSolveWaves) {
-        const int chunk = task % nchunk, grp = task / nchunk;
-        const int c = c0 + chunk * lpr + cl;
-        const bool live = c < ce;
-        double u[NB];
+// 32 rows x 32 columns of A22 -= L21 U12 by one wave on the float64 matrix
+// cores: load, multiply, store.  sl: -L21, depth k and row r at k ls + r; su:
+// U12, depth k and column c at k us + c; nd: the depth, a multiple of 4.  CHAIN:
+// the products are added to A22 one by one, as the elimination of a pivot row
+// adds them, so that equal rows stay equal; else they are summed by themselves
+// and added once (one rounding of A22 per panel, not one per column).  The tile is formed transposed (matrix columns as the MFMA's
+// rows), so that an access's 16 lanes are 16 consecutive rows of one column: 128
+// bytes.
+template <bool CHAIN>
+struct UpdateTile {
+    d4v c22[2][2], acc[2][2];
+    __device__ __forceinline__ void load(const double* A, long long m, long long row0, long long col0, long long row_end,
+                                         long long col_end) {
+        const int lane = threadIdx.x % kWave, r = lane % 16, q = lane / 16;
 #pragma unroll
-        for (int j = 0; j < NB; ++j) u[j] = (live && j < nb) ? A[(k0 + j) * ld + c] : 0.0;
-        for (int i0 = c0 + (grp * sets + sub) * RB; i0 < m; i0 += groups * sets * RB) {
-            double v[RB];
+        for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-            for (int q = 0; q < RB; ++q) v[q] = (live && i0 + q < m) ? A[(i0 + q) * ld + c] : 0.0;
+            for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-            for (int q = 0; q < RB; ++q) {
-                if (i0 + q < m) {
-                    const double* Lr = L.panel + (i0 + q - k0) * NB;
-#pragma unroll
-                    for (int j = 0; j < NB; ++j) v[q] = __builtin_fma(-Lr[j], u[j], v[q]);
+                for (int i = 0; i < 4; ++i) {
+                    const long long col = col0 + 16 * ct + q + 4 * i, row = row0 + 16 * rt + r;
+                    c22[ct][rt][i] = (col < col_end && row < row_end) ? A[col * m + row] : 0.0;
                 }
+    }
+    __device__ __forceinline__ void multiply(const double* sl, int ls, const double* su, int us, int nd) {
+        const int lane = threadIdx.x % kWave, r = lane % 16, q = lane / 16;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t / 2][t % 2] = CHAIN ? c22[t / 2][t % 2] : d4v{0.0, 0.0, 0.0, 0.0};
+        for (int k = 0; k < nd; k += 4) {
+            double x[2], y[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                x[t] = su[(k + q) * us + 16 * t + r];
+                y[t] = sl[(k + q) * ls + 16 * t + r];
             }
 #pragma unroll
-            for (int q = 0; q < RB; ++q)
-                if (live && i0 + q < m) A[(i0 + q) * ld + c] = v[q];
+            for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt)
+                    acc[ct][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[ct], y[rt], acc[ct][rt], 0, 0, 0);
         }
     }
-}
+    __device__ __forceinline__ void store(double* A, long long m, long long row0, long long col0, long long row_end,
+                                          long long col_end) const {
+        const int lane = threadIdx.x % kWave, r = lane % 16, q = lane / 16;
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const long long col = col0 + 16 * ct + q + 4 * i, row = row0 + 16 * rt + r;
+                    if (col < col_end && row < row_end) A[col * m + row] = CHAIN ? acc[ct][rt][i] : c22[ct][rt][i] + acc[ct][rt][i];
+                }
+    }
+};
 
-// Back substitution with U in A[0 .. m)[0 .. m) and the right-hand sides in
-// columns m .. m+nr; buf: LDS of buf_doubles >= kBackBlock (kBackBlock + 1) + m.
-__device__ void back_substitute(const double* A, long long ld, int m, int nr, double* x, double* buf,
-                                int buf_doubles) {
-    const int t = threadIdx.x;
-    const int lane = t % kWave, wave = t / kWave;
-    double* Ub = buf;                                    // [kBackBlock][kBackBlock + 1]
-    double* Xs = buf + kBackBlock * (kBackBlock + 1);    // [m][rc]
-    const int rc_max = (buf_doubles - kBackBlock * (kBackBlock + 1)) / m;
-    for (int r0 = 0; r0 < nr; r0 += rc_max) {
-        const int rc = min(rc_max, nr - r0);
+// Back substitution inside rows lo .. hi - 1 (hi - lo <= kBackRows) for rc <=
+// kBackRhs right-hand sides from column m + r0 of A on: the block's solution
+// goes back to those columns and to x.  In diagonal blocks of kBackBlock rows
+// from the bottom: one wave per right-hand side solves the diagonal block
+// (lanes over its rows), then threads over rows update the rest of the block.
+constexpr int kBackBlock = 64;
+constexpr int kBackRows = 512;
+constexpr int kBackRhs = kSolveWaves;
+struct BackLds {
+    double u[kBackBlock][kBackBlock + 1];    // a diagonal block of U: [column][row]
+    double y[kBackRhs][kBackRows];
+};
+__device__ inline void back_block(double* A, long long m, int lo, int hi, int r0, int rc, double* x, BackLds& L) {
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    for (int e = t; e < rc * kBackRows; e += kSolveThreads) {
+        const int c = e / kBackRows, i = e % kBackRows;
+        if (lo + i < hi) L.y[c][i] = A[(m + r0 + c) * m + lo + i];
+    }
+    for (int ie = hi; ie > lo; ie -= kBackBlock) {
+        const int ib = max(lo, ie - kBackBlock), bs = ie - ib;
+        for (int e = t; e < kBackBlock * kBackBlock; e += kSolveThreads) {
+            const int c = e / kBackBlock, r = e % kBackBlock;
+            if (c < bs && r <= c) L.u[c][r] = A[(ib + c) * m + ib + r];
+        }
         __syncthreads();
-        for (int e = t; e < m * rc; e += kSolveThreads) {
-            const int q = e / rc, c = e - q * rc;
-            Xs[e] = A[q * ld + m + r0 + c];
-        }
-        for (int ie = m; ie > 0; ie -= kBackBlock) {
-            const int ib = max(0, ie - kBackBlock), bs = ie - ib;
-            for (int e = t; e < bs * bs; e += kSolveThreads) {
-                const int r = e / bs, c = e - r * bs;
-                Ub[r * (kBackBlock + 1) + c] = A[(ib + r) * ld + ib + c];
-            }
-            __syncthreads();
-            // diagonal block: one wave per right-hand side, lanes over its rows
-            for (int c = wave; c < rc; c += kSolveWaves) {
-                double xv = lane < bs ? Xs[(ib + lane) * rc + c] : 0.0;
+        if (wave < rc) {
+            double xv = lane < bs ? L.y[wave][ib - lo + lane] : 0.0;
+            const double ud = lane < bs ? L.u[lane][lane] : 1.0, uinv = 1.0 / ud;
+            if (__all(plain_exponent((unsigned)(__double_as_longlong(ud) >> 32) & 0x7fffffffu))) {
+                // y / u from the reciprocal with one correction step
                 for (int i = bs - 1; i >= 0; --i) {
-                    const double xi = lane_value(xv, i) / Ub[i * (kBackBlock + 1) + i];
-                    if (lane == i) xv = xi;
-                    else if (lane < i) xv = __builtin_fma(-Ub[lane * (kBackBlock + 1) + i], xi, xv);
+                    const double yi = lane_value(xv, i), u = lane_value(ud, i), v = lane_value(uinv, i);
+                    const double ui = L.u[i][lane];
+                    double xi = yi * v;
+                    xi = __builtin_fma(__builtin_fma(-xi, u, yi), v, xi);
+                    xv = lane == i ? xi : (lane < i ? __builtin_fma(-ui, xi, xv) : xv);
                 }
-                if (lane < bs) Xs[(ib + lane) * rc + c] = xv;
+            } else {
+                for (int i = bs - 1; i >= 0; --i) {
+                    const double xi = lane_value(xv, i) / lane_value(ud, i);
+                    const double ui = L.u[i][lane];
+                    xv = lane == i ? xi : (lane < i ? __builtin_fma(-ui, xi, xv) : xv);
+                }
             }
-            __syncthreads();
-            // rows above the block: X[q] -= U[q][ib .. ie) X[ib .. ie)
-            for (int e = t; e < ib * rc; e += kSolveThreads) {
-                const int q = e / rc, c = e - q * rc;
-                const double* Uq = A + (long long)q * ld + ib;
-                double acc = 0.0;
-#pragma unroll 8
-                for (int j = 0; j < bs; ++j) acc = __builtin_fma(Uq[j], Xs[(ib + j) * rc + c], acc);
-                Xs[e] -= acc;
+            if (lane < bs) {
+                L.y[wave][ib - lo + lane] = xv;
+                A[(m + r0 + wave) * m + ib + lane] = xv;
+                x[(long long)(r0 + wave) * m + ib + lane] = xv;
             }
-            __syncthreads();
         }
-        for (long long e = t; e < (long long)rc * m; e += kSolveThreads) {
-            const int c = (int)(e / m), i = (int)(e - (long long)c * m);
-            x[(long long)(r0 + c) * m + i] = Xs[i * rc + c];
+        __syncthreads();
+        const int rows = ib - lo;
+        for (int e = t; e < rows * rc; e += kSolveThreads) {
+            const int c = e / rows, i = e - c * rows;
+            const double* U = A + (long long)ib * m + lo + i;
+            double acc = 0.0;
+            int j = 0;
+            for (; j + 16 <= bs; j += 16) {
+                double v[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) v[k] = U[(long long)(j + k) * m];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) acc = __builtin_fma(v[k], L.y[c][ib - lo + j + k], acc);
+            }
+            for (; j < bs; ++j) acc = __builtin_fma(U[(long long)j * m], L.y[c][ib - lo + j], acc);
+            L.y[c][i] -= acc;
         }
+        __syncthreads();
     }
 }
 
-template <int NB>
+constexpr int kOuterNB = 32;               // columns per outer panel
+constexpr int kMultiMin = 384;             // systems of at least this many unknowns take the multi-work-group path
+constexpr int kOneRows = kMultiMin + 48;   // LDS row stride of L21 in the one-work-group path: the rows and a tile's
+                                           // remainder, 16 mod 32 (no conflicts)
+constexpr int kOneCols = 128;              // columns of U12 staged at a time there
+constexpr int kOneColStride = kOneCols + 16;
+
+// LDS of the one-work-group elimination.
+struct OneLds {
+    double l[kOuterNB][kOneRows];            // -L21 and -L11 by columns (rows of the panel)
+    double u[kOuterNB][kOneColStride];       // U12
+    PivotLds<kOuterNB> p;
+    int src[kOuterNB], dst[kOuterNB], moved;
+};
+
+// Factorise one panel there: U11 to A, the multipliers to L.l, the exchanges to L.src and L.dst.
+template <int RPT>
+__device__ __forceinline__ void one_panel(double* A, long long m, int k0, int mr, int nb, int waves, OneLds& L) {
+    constexpr int NB = kOuterNB;
+    PanelRows<NB, RPT> R;
+    load_rows<NB, RPT>(R, A, m, k0, mr, nb, waves);
+    factor_rows<NB, RPT>(R, nb, waves, L.p);
+    if (waves == 1) __syncthreads();         // blk and piv for every wave (the last column's barrier otherwise)
+    if (L.p.sing) return;                    // positions hold nothing of use then
+    put_rows(R, L.p, nb, [&](int r, int c, double v) {
+        L.l[c][r] = -v;
+        if (r < nb) A[(k0 + c) * m + k0 + r] = v;
+    });
+    compose_moves(L.p, nb, L.src, L.dst, &L.moved);
+}
+
+// The whole solve in one work-group (m < kMultiMin), the matrix in the caller's
+// workspace (L2).  Bound by the panels' column chains (about 1 us per column).
 __global__ void __launch_bounds__(kSolveThreads) master_solve_kernel(SolveArgs a) {
-    __shared__ PanelLds<NB> L;
-    const int t = threadIdx.x;
-    const int lane = t % kWave, wave = t / kWave;
-    const int m = a.m, nr = a.n_rhs;
-    const long long ld = (long long)m + nr;
+    constexpr int NB = kOuterNB;
+    struct Tile {
+        double v[kBackBlock][kBackBlock + 1];
+    };
+    __shared__ union Lds {
+        OneLds e;
+        Tile t;
+        BackLds b;
+    } S;
+    const int t = threadIdx.x, wave = t / kWave;
+    const int m = a.m, nr = a.n_rhs, ld = m + nr;
     double* A = a.work;
 
-    // assemble [K | C~]
-    for (int r = wave; r < m; r += kSolveWaves)
-        for (int c = lane; c < (int)ld; c += kWave) A[r * ld + c] = assembled(a, r, c);
+    // assemble [K | C~] by columns through LDS tiles
+    for (int c0 = 0; c0 < ld; c0 += kBackBlock)
+        for (int r0 = 0; r0 < m; r0 += kBackBlock) {
+            for (int e = t; e < kBackBlock * kBackBlock; e += kSolveThreads) {
+                // rows of K are contiguous; a right-hand side is contiguous over r
+                const int r = e / kBackBlock, c = e % kBackBlock;
+                if (r0 + r < m && c0 + c < ld) S.t.v[c][r] = assembled(a, r0 + r, c0 + c);
+            }
+            __syncthreads();
+            for (int e = t; e < kBackBlock * kBackBlock; e += kSolveThreads) {
+                const int c = e / kBackBlock, r = e % kBackBlock;
+                if (r0 + r < m && c0 + c < ld) A[(long long)(c0 + c) * m + r0 + r] = S.t.v[c][r];
+            }
+            __syncthreads();
+        }
+    if (t == 0) S.e.p.sing = S.e.moved = 0;
     __syncthreads();
 
     bool singular = false;
     for (int k0 = 0; k0 < m; k0 += NB) {
-        const int nb = min(NB, m - k0);
-        const int mr = m - k0;
-        // panel: rows k0 .. m-1, columns k0 .. k0+nb-1
-        load_panel<NB>(L, A, ld, k0, mr, nb);
-        __syncthreads();
-        singular = factor_panel<NB>(L, mr, nb);
-        if (singular) break;
-        // U11 back to A; right of the panel: the row exchanges, then U12 = L11^-1 A12
-        for (int e = t; e < nb * nb; e += kSolveThreads) {
-            const int r = e / nb, j = e - r * nb;
-            A[(k0 + r) * ld + k0 + j] = L.panel[r * NB + j];
+        const int nb = min(NB, m - k0), mr = m - k0;
+        {
+            // at most 128 rows: two per lane of one wave, no barriers
+            if (mr <= 2 * kWave)
+                one_panel<2>(A, m, k0, mr, nb, 1, S.e);
+            else
+                one_panel<1>(A, m, k0, mr, nb, (mr + kWave - 1) / kWave, S.e);
         }
-        for (int c = k0 + nb + t; c < (int)ld; c += kSolveThreads) exchange_and_solve_column<NB>(A, ld, k0, nb, L, c, true);
         __syncthreads();
-        panel_trailing_update<NB, kRowBatch>(A, ld, m, k0, nb, (int)ld, L);
-        __syncthreads();
+        singular = S.e.p.sing != 0;
+        if (singular) break;
+        const bool moved = S.e.moved != 0;
+        for (int c0 = k0 + nb; c0 < ld; c0 += kOneCols) {
+            const int w = min(kOneCols, ld - c0);
+            if (t < kOneCols) {
+                double u[NB];
+#pragma unroll
+                for (int i = 0; i < NB; ++i) u[i] = 0.0;
+                if (t < w)
+                    move_and_solve<NB>(A + (long long)(c0 + t) * m + k0, nb, moved, S.e.src, S.e.dst, &S.e.l[0][0],
+                                       kOneRows, 1.0, true, u);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) S.e.u[i][t] = u[i];
+            }
+            __syncthreads();
+            const int tr = (mr - nb + 31) / 32, tc = (w + 31) / 32;
+            for (int e = wave; e < tr * tc; e += kSolveWaves) {
+                const int ir = e % tr, ic = e / tr;
+                UpdateTile<true> T;
+                T.load(A, m, k0 + nb + 32 * ir, c0 + 32 * ic, m, c0 + w);
+                T.multiply(&S.e.l[0][nb + 32 * ir], kOneRows, &S.e.u[0][32 * ic], kOneColStride, NB);
+                T.store(A, m, k0 + nb + 32 * ir, c0 + 32 * ic, m, c0 + w);
+            }
+            __syncthreads();
+        }
+        if (t == 0) S.e.moved = 0;           // the next panel's barriers order this before its moves
     }
 
     if (singular) {
         for (long long e = t; e < (long long)nr * m; e += kSolveThreads) a.x[e] = __builtin_nan("");
         return;
     }
-    // back substitution; the panel buffer is free now
-    back_substitute(A, ld, m, nr, a.x, L.panel, kPanelDoubles);
+    for (int r0 = 0; r0 < nr; r0 += kBackRhs) {
+        __syncthreads();
+        back_block(A, m, 0, m, r0, min(kBackRhs, nr - r0), a.x, S.b);
+    }
 }
 
 // ---------------------------------------------------------------------------
 // Multi-work-group path (m >= kMultiMin).
-constexpr int kOuterNB = 32;               // columns per outer panel
 constexpr int kSingularSlot = kOuterNB;    // x[kSingularSlot]: an outer panel met a zero pivot
 constexpr int kSwapCols = 64;              // columns per work-group of the swap + TRSM kernel
 constexpr int kSwapThreads = 256;
-constexpr int kUpdTile = 64;               // the update kernel's tile: kUpdTile x kUpdTile entries
-constexpr int kUpdThreads = 256;           // 16 x 16 threads, 4 x 4 entries each
-constexpr int kBackDoubles = 20000;        // back-substitution LDS (m <= 15840 with one right-hand side)
+static_assert(kWave % kOuterNB == 0, "a column's touched rows are read by one wave");
+constexpr int kUpdTile = 64;               // the update kernel's tile: 4 waves of 32 x 32
+constexpr int kUpdThreads = 256;
+constexpr int kUpdStride = kUpdTile + 16;  // LDS stride of its operands (16 mod 32: no conflicts)
+constexpr int kAboveRows = 64;             // rows per work-group of solve_back_above_kernel
 static_assert(kOuterNB <= kWave, "the swap kernel's mapping keeps two touched rows per lane of one wave");
-constexpr int kPanelRowBatch = 16;         // rows loaded before any is stored in the panel kernel's update
-                                           // (half that for 8-column panels, which would spill)
-constexpr int kMultiMin = 400;             // systems of at least this many unknowns take this path
 static_assert(kMultiMin > kSingularSlot, "x must hold the pivots and the flag");
-static_assert(kSolveMaxCols - 1 <= kPanelDoubles, "every panel's rows must fit an LDS panel of one column");
-static_assert(kBackBlock * (kBackBlock + 1) + kSolveMaxCols <= kBackDoubles,
-              "back substitution holds at least one right-hand side of every system in LDS");
+static_assert(kMultiMin <= kBackRows && kMultiMin <= kSolveThreads, "one row per thread and one back block below it");
 
 struct OuterArgs {
-    double* A;                   // the augmented matrix [m][ld]
-    double* x;                   // pivots of the outer panel in x[0 .. nbo), the flag in x[kSingularSlot]
-    long long ld;
-    int m, k0, nbo;
+    double* A;                   // the augmented matrix by columns: m + n_rhs columns of m
+    double* x;                   // pivots of the outer panel in x[0 .. kOuterNB), the flag in x[kSingularSlot]
+    long long ld;                // columns
+    int m, k0, nbo;              // outer panel: columns k0 .. k0 + nbo - 1
+    int kk, nb;                  // panel and update kernels: columns kk .. kk + nb - 1 of it
+    long long c0, c1;            // update kernel: columns c0 .. c1 - 1
 };
 
+// 32 x 32 tiles of [K | C~] through LDS, from rows of K to columns of the workspace.
+constexpr int kAsmTile = 32;
 __global__ void __launch_bounds__(256) solve_assemble_kernel(SolveArgs a) {
-    const int r = blockIdx.x;
-    const long long ld = (long long)a.m + a.n_rhs;
-    for (int c = threadIdx.x; c < (int)ld; c += 256) a.work[r * ld + c] = assembled(a, r, c);
+    __shared__ double v[kAsmTile][kAsmTile + 1];
+    const int r0 = blockIdx.y * kAsmTile, c0 = blockIdx.x * kAsmTile;
+    const int lo = threadIdx.x % kAsmTile, up = threadIdx.x / kAsmTile;
+    const int ld = a.m + a.n_rhs;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.x[kSingularSlot] = 0.0;
+#pragma unroll
+    for (int q = 0; q < kAsmTile; q += 8)
+        if (r0 + up + q < a.m && c0 + lo < ld) v[up + q][lo] = assembled(a, r0 + up + q, c0 + lo);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kAsmTile; q += 8)
+        if (r0 + lo < a.m && c0 + up + q < ld) a.work[(long long)(c0 + up + q) * a.m + r0 + lo] = v[lo][up + q];
 }
 
-// One work-group factorises the outer panel: columns k0 .. k0+nbo-1, rows
-// k0 .. m-1, in inner panels of NB columns.  Every inner panel is written back
-// whole (its multipliers are the L21 of the update kernel), its row exchanges
-// go to the outer panel's other columns (left ones too, so L21 stays in row
-// order) and its U12 and trailing update stay inside the outer panel.
-template <int NB>
-__global__ void __launch_bounds__(kSolveThreads) solve_panel_kernel(OuterArgs a) {
-    __shared__ PanelLds<NB> L;
+// One work-group factorises columns kk .. kk + nb - 1 (rows kk .. m - 1) of the
+// outer panel in registers and applies the exchanges to the outer panel's
+// other columns, with U12 for those on the right.  Bound by one compute unit's
+// reach: the column chains (2000 .. 3000 clocks each) and, for tall panels, its
+// loads and stores (10 .. 15 bytes per clock).  Per 32 columns at about 3000
+// rows: 4 launches of 25 us (one of 220 us before, which streamed the outer
+// panel through L2 for every inner panel's update).
+template <int NB, int RPT, int T = kSolveThreads>
+__global__ void __launch_bounds__(T) solve_panel_kernel(OuterArgs a) {
+    __shared__ PivotLds<NB> P;
+    __shared__ double s_l[NB][NB];           // L11 by columns
+    __shared__ int s_src[NB], s_dst[NB], s_moved;
     const int t = threadIdx.x;
-    const int m = a.m, k0 = a.k0, ce = a.k0 + a.nbo;
-    const long long ld = a.ld;
+    const int m = a.m, kk = a.kk, nb = a.nb, mr = m - kk;
     double* A = a.A;
-    if (k0 == 0) {
-        if (t == 0) a.x[kSingularSlot] = 0.0;
-    } else if (a.x[kSingularSlot] != 0.0) {
-        return;                                   // an earlier panel was singular
+    if (a.x[kSingularSlot] != 0.0) return;   // an earlier panel was singular
+    if (t == 0) P.sing = s_moved = 0;
+    __syncthreads();
+    const int waves = min((int)blockDim.x, mr + kWave - 1) / kWave;
+    PanelRows<NB, RPT> R;
+    load_rows<NB, RPT>(R, A, m, kk, mr, nb, waves);
+    factor_rows<NB, RPT>(R, nb, waves, P);
+    if (waves == 1) __syncthreads();         // blk and piv for every wave (the last column's barrier otherwise)
+    if (P.sing) {                            // positions hold nothing of use then
+        if (t == 0) a.x[kSingularSlot] = 1.0;
+        return;
     }
-    for (int kk = k0; kk < ce; kk += NB) {
-        const int nb = min(NB, ce - kk), mr = m - kk;
-        load_panel<NB>(L, A, ld, kk, mr, nb);
-        __syncthreads();
-        if (factor_panel<NB>(L, mr, nb)) {
-            if (t == 0) a.x[kSingularSlot] = 1.0;
-            return;
+    put_rows(R, P, nb, [&](int r, int c, double v) {
+        A[(long long)(kk + c) * m + kk + r] = v;
+        if (r < NB) s_l[c][r] = v;
+    });
+    if constexpr (NB < kOuterNB) compose_moves(P, nb, s_src, s_dst, &s_moved);
+    __syncthreads();
+    if (t < nb) a.x[kk - a.k0 + t] = (double)(kk + P.piv[t]);
+    if constexpr (NB < kOuterNB) {
+        const int nleft = kk - a.k0, nother = nleft + (a.k0 + a.nbo - kk - nb);
+        if (t < nother) {
+            const int c = t < nleft ? a.k0 + t : kk + nb + (t - nleft);
+            double u[NB];
+            move_and_solve<NB>(A + (long long)c * m + kk, nb, s_moved != 0, s_src, s_dst, &s_l[0][0], NB, -1.0,
+                               t >= nleft, u);
         }
-        for (int e = t; e < mr * nb; e += kSolveThreads) {
-            const int r = e / nb, j = e - r * nb;
-            A[(kk + r) * ld + kk + j] = L.panel[r * NB + j];
-        }
-        if (t < nb) a.x[kk - k0 + t] = (double)(kk + L.perm[t]);
-        if (t == 0) compose_exchanges<NB>(L, nb);
-        __syncthreads();
-        // the other columns of the outer panel: left ones get the exchanges,
-        // right ones the exchanges and U12
-        const int nleft = kk - k0, nother = nleft + (ce - kk - nb);
-        for (int q = t; q < nother; q += kSolveThreads) {
-            const int c = q < nleft ? k0 + q : kk + nb + (q - nleft);
-            permute_and_solve_column<NB>(A, ld, kk, nb, L, c, q >= nleft);
-        }
-        __syncthreads();
-        if (kk + nb < ce) panel_trailing_update<NB, (NB >= 8 ? kPanelRowBatch / 2 : kPanelRowBatch)>(A, ld, m, kk, nb, ce, L);
-        __syncthreads();
     }
 }
 
@@ -576,48 +824,40 @@ __global__ void __launch_bounds__(kSolveThreads) solve_panel_kernel(OuterArgs a)
 // exchanges of the panel composed into one permutation of the rows they touch
 // (the top block k0 .. k0+nbo-1 and at most nbo rows below it), applied by
 // reading every source row before writing any, then U12 = L11^-1 A12 for the
-// top block (one thread per column).
+// top block, one thread per column.  The top block passes through LDS both ways, so
+// that memory is read and written along columns (a thread per column there
+// touched 64 cache lines per access: 13.7 us per launch at 4000 unknowns, now 10.6).
 __global__ void __launch_bounds__(kSwapThreads) solve_swap_trsm_kernel(OuterArgs a) {
-    __shared__ double s_l[kOuterNB][kOuterNB + 1];
-    __shared__ double s_tile[2 * kOuterNB][kSwapCols];
+    __shared__ double s_tile[kSwapCols][kOuterNB + 1];
+    __shared__ double s_l[kOuterNB][kOuterNB];   // L11 by columns
     __shared__ int s_row[2 * kWave];             // touched rows: the top block first (two per lane)
     __shared__ int s_src[2 * kWave];             // the row whose old values land in s_row[i]
-    __shared__ int s_n;
-    if (a.x[kSingularSlot] != 0.0) return;
     const int t = threadIdx.x;
-    const int lane = t % kSwapCols, grp = t / kSwapCols;
-    constexpr int kGroups = kSwapThreads / kSwapCols;
     const int k0 = a.k0, nbo = a.nbo;
-    const long long ld = a.ld;
-    const double* Ac = a.A;
-    const long long c = (long long)(k0 + nbo) + (long long)blockIdx.x * kSwapCols + lane;
-    const bool live = c < ld;
-    // L11: every thread issues its 16 loads before it stores any
-    {
-        constexpr int kPer = kOuterNB * kOuterNB / kSwapThreads;
-        double v[kPer];
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int e = t + q * kSwapThreads, r = e / kOuterNB, j = e - r * kOuterNB;
-            v[q] = (r < nbo && j < nbo) ? Ac[(k0 + r) * ld + k0 + j] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int e = t + q * kSwapThreads, r = e / kOuterNB, j = e - r * kOuterNB;
-            s_l[r][j] = v[q];
-        }
+    const long long m = a.m;
+    const long long c0 = (long long)k0 + nbo;
+    const double flag = a.x[kSingularSlot];
+    // after the last panel: the flag moves into an entry of L that is no longer read
+    if (c0 == m && blockIdx.x == 0 && t == 0) a.A[m - 1] = flag;
+    if (flag != 0.0) return;
+    for (int e = t; e < kOuterNB * kOuterNB; e += kSwapThreads) {
+        const int c = e / kOuterNB, r = e % kOuterNB;
+        s_l[c][r] = (c < nbo && r < nbo) ? a.A[(k0 + c) * m + k0 + r] : 0.0;
     }
+    __shared__ int s_n;                          // touched rows (0: no row moves)
     if (t < kWave) {
-        // one wave: lane i keeps touched rows i and i + 64 in registers; a
-        // ballot finds where the pivot row sits
+        // one wave: lane i keeps touched rows i and i + 64 in registers; a ballot
+        // finds where the pivot row sits
         const int l = t;
+        int n = nbo;
+        bool moved = false;
         int row0 = l < nbo ? k0 + l : -1, src0 = row0;
         int row1 = -1, src1 = -1;
-        int n = nbo;
         const int piv = l < nbo ? (int)a.x[l] : 0;       // all pivots in one load
         for (int j = 0; j < nbo; ++j) {
-            const int p = __shfl(piv, j);
+            const int p = __builtin_amdgcn_readlane(piv, j);
             if (p == k0 + j) continue;
+            moved = true;
             const unsigned long long h0 = __ballot(row0 == p), h1 = __ballot(row1 == p);
             int ip;
             if (h0) {
@@ -643,100 +883,128 @@ __global__ void __launch_bounds__(kSwapThreads) solve_swap_trsm_kernel(OuterArgs
         s_src[l] = src0;
         s_row[kWave + l] = row1;
         s_src[kWave + l] = src1;
-        if (l == 0) s_n = n;
+        if (l == 0) s_n = moved ? n : 0;
     }
     __syncthreads();
     const int n = s_n;
-    {
-        constexpr int kPer = 2 * kOuterNB / kGroups;     // touched rows per thread, loaded before any store
-        double v[kPer];
+    const long long cb = c0 + (long long)blockIdx.x * kSwapCols;
+    const int w = (int)(a.ld - cb < kSwapCols ? a.ld - cb : kSwapCols);
+    // lanes over the top block's rows, two columns per wave and pass
+    constexpr int kPer = kSwapCols * kOuterNB / kSwapThreads;
+    const int i = t % kOuterNB, g = t / kOuterNB;
+    const bool top = i < nbo;
+    double v[kPer], d[kPer];
+    const int from = !top ? k0 : n ? s_src[i] : k0 + i;
+    const bool down = nbo + i < n;
+    const int dfrom = down ? s_src[nbo + i] : k0, dto = down ? s_row[nbo + i] : k0;
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int i = grp + q * kGroups;
-            v[q] = (i < n && live) ? Ac[(long long)s_src[i] * ld + c] : 0.0;
-        }
+    for (int q = 0; q < kPer; ++q) {
+        const int c = g + q * (kSwapThreads / kOuterNB);
+        const double* Ac = a.A + (cb + min(c, w - 1)) * m;
+        v[q] = Ac[from];
+        if (n) d[q] = Ac[dfrom];
+    }
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int i = grp + q * kGroups;
-            if (i < n) s_tile[i][lane] = v[q];
-        }
+    for (int q = 0; q < kPer; ++q) {
+        const int c = g + q * (kSwapThreads / kOuterNB);
+        s_tile[c][i] = v[q];
+        // each column's rows are all read (by lanes of this same wave) before this writes any
+        if (down && c < w) a.A[(cb + c) * m + dto] = d[q];
     }
     __syncthreads();
-    if (!live) return;
-    double* A = a.A;
-    for (int i = nbo + grp; i < n; i += kGroups) A[(long long)s_row[i] * ld + c] = s_tile[i][lane];
-    if (grp == 0) {
-        for (int j = 0; j < nbo; ++j) {
-            double v = s_tile[j][lane];
-            for (int i = 0; i < j; ++i) v = __builtin_fma(-s_l[j][i], s_tile[i][lane], v);
-            s_tile[j][lane] = v;
-            A[(k0 + j) * ld + c] = v;
+    if (t < kSwapCols) {
+        double u[kOuterNB];
+#pragma unroll
+        for (int r = 0; r < kOuterNB; ++r) u[r] = s_tile[t][r];
+        int ofs = 0;
+#pragma unroll
+        for (int r = 0; r < kOuterNB; ++r) {
+            asm volatile("" : "+v"(ofs), "+v"(u[r]));   // a column of L11 is read when its turn comes, not before
+#pragma unroll
+            for (int j = r + 1; j < kOuterNB; ++j) u[j] = __builtin_fma(-s_l[r][ofs + j], u[r], u[j]);
         }
+#pragma unroll
+        for (int r = 0; r < kOuterNB; ++r) s_tile[t][r] = u[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int c = g + q * (kSwapThreads / kOuterNB);
+        if (top && c < w) a.A[(cb + c) * m + k0 + i] = s_tile[c][i];
     }
 }
 
-// A22 -= L21 U12 over rows and columns k0+nbo .. (m and ld), depth nbo:
-// kUpdTile x kUpdTile entries per work-group, 4 x 4 per thread.
+// A22 -= L21 U12 over rows kk+nb .. m-1 and columns c0 .. c1-1, depth nb:
+// kUpdTile x kUpdTile entries per work-group, one 32 x 32 quarter per wave.
+// Bound by the trailing matrix's traffic, 16 bytes per entry and outer panel:
+// 65 us for the first one at 4000 unknowns (94 us before, on the vector unit,
+// one work-group's loads after another).
 __global__ void __launch_bounds__(kUpdThreads) solve_update_kernel(OuterArgs a) {
-    __shared__ double s_lt[kOuterNB][kUpdTile + 1];    // L21 transposed: [k][row]
-    __shared__ double s_u[kOuterNB][kUpdTile];         // U12: [k][column]
+    __shared__ double s_l[kOuterNB * kUpdStride];      // -L21: [k][row]
+    __shared__ double s_u[kOuterNB * kUpdStride];      // U12: [k][column]
     if (a.x[kSingularSlot] != 0.0) return;
     const int t = threadIdx.x;
-    const int tr = t / 16, tc = t % 16;
-    const int k0 = a.k0, nbo = a.nbo, m = a.m;
-    const long long ld = a.ld;
-    const long long c0 = (long long)k0 + nbo;
-    const long long rb = c0 + (long long)blockIdx.y * kUpdTile, cb = c0 + (long long)blockIdx.x * kUpdTile;
+    const long long m = a.m;
+    const int kk = a.kk, nb = a.nb, nd = (nb + 3) / 4 * 4;
+    const long long rb = (long long)kk + nb + (long long)blockIdx.x * kUpdTile;
+    const long long cb = a.c0 + (long long)blockIdx.y * kUpdTile;
     double* A = a.A;
-    for (int e = t; e < kUpdTile * kOuterNB; e += kUpdThreads) {
-        const int r = e / kOuterNB, k = e - r * kOuterNB;
-        s_lt[k][r] = (k < nbo && rb + r < m) ? A[(rb + r) * ld + k0 + k] : 0.0;
+    for (int e = t; e < kUpdTile * nd; e += kUpdThreads) {
+        const int k = e / kUpdTile, r = e % kUpdTile;
+        s_l[k * kUpdStride + r] = (k < nb && rb + r < m) ? -A[(kk + k) * m + rb + r] : 0.0;
     }
-    for (int e = t; e < kOuterNB * kUpdTile; e += kUpdThreads) {
-        const int k = e / kUpdTile, cc = e - k * kUpdTile;
-        s_u[k][cc] = (k < nbo && cb + cc < ld) ? A[(k0 + k) * ld + cb + cc] : 0.0;
+    for (int e = t; e < kUpdTile * nd; e += kUpdThreads) {
+        const int cc = e / nd, k = e - cc * nd;
+        s_u[k * kUpdStride + cc] = (k < nb && cb + cc < a.c1) ? A[(cb + cc) * m + kk + k] : 0.0;
     }
     __syncthreads();
-    double acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-    for (int k = 0; k < nbo; ++k) {
-        double l[4], u[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            l[q] = s_lt[k][tr * 4 + q];
-            u[q] = s_u[k][tc * 4 + q];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fma(l[i], u[j], acc[i][j]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const long long r = rb + tr * 4 + i;
-        if (r >= m) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const long long c = cb + tc * 4 + j;
-            if (c < ld) A[r * ld + c] -= acc[i][j];
-        }
-    }
+    const int wave = t / kWave, wr = 32 * (wave % 2), wc = 32 * (wave / 2);
+    if (rb + wr >= m || cb + wc >= a.c1) return;
+    UpdateTile<false> T;
+    T.load(A, m, rb + wr, cb + wc, m, a.c1);
+    T.multiply(s_l + wr, kUpdStride, s_u + wc, kUpdStride, nd);
+    T.store(A, m, rb + wr, cb + wc, m, a.c1);
 }
 
-__global__ void __launch_bounds__(kSolveThreads) solve_back_kernel(SolveArgs a) {
-    __shared__ double buf[kBackDoubles];
-    const int t = threadIdx.x;
-    const int m = a.m, nr = a.n_rhs;
-    const bool singular = a.x[kSingularSlot] != 0.0;
-    __syncthreads();                              // every thread has read the flag before x is written
-    if (singular) {
-        for (long long e = t; e < (long long)nr * m; e += kSolveThreads) a.x[e] = __builtin_nan("");
+struct BackArgs {
+    double* A;
+    double* x;                   // [n_rhs][m]
+    int m, n_rhs, lo, hi;        // rows lo .. hi - 1 of this block
+};
+
+// kBackRhs right-hand sides per work-group.
+__global__ void __launch_bounds__(kSolveThreads) solve_back_block_kernel(BackArgs a) {
+    __shared__ BackLds L;
+    const int r0 = blockIdx.x * kBackRhs, rc = min(kBackRhs, a.n_rhs - r0);
+    if (a.A[a.m - 1] != 0.0) {                // singular
+        for (int c = 0; c < rc; ++c)
+            for (int i = a.lo + threadIdx.x; i < a.hi; i += kSolveThreads)
+                a.x[(long long)(r0 + c) * a.m + i] = __builtin_nan("");
         return;
     }
-    back_substitute(a.work, (long long)m + nr, m, nr, a.x, buf, kBackDoubles);
+    back_block(a.A, a.m, a.lo, a.hi, r0, rc, a.x, L);
+}
+
+// Rows r < lo of right-hand side blockIdx.y: y[r] -= sum over the block's columns
+// of U[r][c] x[c]; kAboveRows rows per work-group, its waves take every fourth column.
+__global__ void __launch_bounds__(256) solve_back_above_kernel(BackArgs a) {
+    __shared__ double s_x[kBackRows];
+    __shared__ double s_p[4][kAboveRows];
+    const long long m = a.m;
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    double* y = a.A + (m + blockIdx.y) * m;
+    for (int i = t; i < a.hi - a.lo; i += 256) s_x[i] = y[a.lo + i];
+    __syncthreads();
+    const int r = blockIdx.x * kAboveRows + lane;
+    double acc = 0.0;
+    if (r < a.lo) {
+        const double* U = a.A + (long long)a.lo * m + r;
+#pragma unroll 8
+        for (int c = wave; c < a.hi - a.lo; c += 4) acc = __builtin_fma(U[c * m], s_x[c], acc);
+    }
+    s_p[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && r < a.lo) y[r] -= (s_p[0][lane] + s_p[1][lane]) + (s_p[2][lane] + s_p[3][lane]);
 }
 
 }  // namespace
@@ -796,43 +1064,74 @@ hipError_t launch_master_solve(int pol, int n, const double* K, int n_rhs, const
     a.pol = pol;
     if (a.m + n_rhs > kSolveMaxCols) return hipErrorInvalidValue;
     if (a.m < kMultiMin) {
-        // the widest panel whose m rows fit in LDS (16 columns would spill registers; m < 400 here)
-        if (a.m * 8 <= kPanelDoubles)
-            hipLaunchKernelGGL(master_solve_kernel<8>, dim3(1), dim3(kSolveThreads), 0, s, a);
-        else
-            hipLaunchKernelGGL(master_solve_kernel<4>, dim3(1), dim3(kSolveThreads), 0, s, a);
+        hipLaunchKernelGGL(master_solve_kernel, dim3(1), dim3(kSolveThreads), 0, s, a);
         return hipGetLastError();
     }
     const int m = a.m;
     const long long ld = (long long)m + n_rhs;
-    hipLaunchKernelGGL(solve_assemble_kernel, dim3((unsigned)m), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(solve_assemble_kernel,
+                       dim3((unsigned)((ld + kAsmTile - 1) / kAsmTile), (unsigned)((m + kAsmTile - 1) / kAsmTile)),
+                       dim3(256), 0, s, a);
+    OuterArgs o;
+    o.A = work;
+    o.x = x;
+    o.ld = ld;
+    o.m = m;
+    auto update = [&](long long c0, long long c1) {
+        const long long rows = m - (o.kk + o.nb);
+        if (rows <= 0 || c1 <= c0) return;
+        o.c0 = c0;
+        o.c1 = c1;
+        hipLaunchKernelGGL(solve_update_kernel,
+                           dim3((unsigned)((rows + kUpdTile - 1) / kUpdTile), (unsigned)((c1 - c0 + kUpdTile - 1) / kUpdTile)),
+                           dim3(kUpdThreads), 0, s, o);
+    };
     for (int k0 = 0; k0 < m; k0 += kOuterNB) {
-        OuterArgs o;
-        o.A = work;
-        o.x = x;
-        o.ld = ld;
-        o.m = m;
         o.k0 = k0;
-        o.nbo = min(kOuterNB, m - k0);
-        // the widest inner panel whose rows fit in LDS
-        if ((m - k0) * 8 <= kPanelDoubles)
-            hipLaunchKernelGGL(solve_panel_kernel<8>, dim3(1), dim3(kSolveThreads), 0, s, o);
-        else if ((m - k0) * 4 <= kPanelDoubles)
-            hipLaunchKernelGGL(solve_panel_kernel<4>, dim3(1), dim3(kSolveThreads), 0, s, o);
-        else if ((m - k0) * 2 <= kPanelDoubles)
-            hipLaunchKernelGGL(solve_panel_kernel<2>, dim3(1), dim3(kSolveThreads), 0, s, o);
-        else
-            hipLaunchKernelGGL(solve_panel_kernel<1>, dim3(1), dim3(kSolveThreads), 0, s, o);
-        const long long c0 = (long long)k0 + o.nbo;    // < ld: there is at least one right-hand side
-        const unsigned col_groups = (unsigned)((ld - c0 + kSwapCols - 1) / kSwapCols);
+        o.nbo = std::min(kOuterNB, m - k0);
+        const int ce = k0 + o.nbo;
+        // the widest panel whose rows fit in registers (64 doubles per thread), chosen by
+        // the outer panel's first column
+        const int mr0 = m - k0;
+        const int nb = mr0 <= 2 * kSolveThreads ? 32 : mr0 <= 4 * kSolveThreads ? 16 : mr0 <= 8 * kSolveThreads ? 8
+                       : mr0 <= 16 * kSolveThreads ? 4 : 2;
+        for (int kk = k0; kk < ce; kk += nb) {
+            o.kk = kk;
+            o.nb = std::min(nb, ce - kk);
+            const int mr = m - kk;
+            if (nb == 32 && mr <= kSolveThreads)
+                hipLaunchKernelGGL((solve_panel_kernel<32, 1>), dim3(1), dim3((unsigned)((mr + kWave - 1) / kWave * kWave)), 0, s, o);
+            else if (nb == 32)
+                hipLaunchKernelGGL((solve_panel_kernel<32, 2>), dim3(1), dim3(kSolveThreads), 0, s, o);
+            else if (nb == 16)
+                hipLaunchKernelGGL((solve_panel_kernel<16, 4>), dim3(1), dim3(kSolveThreads), 0, s, o);
+            else if (nb == 8)
+                hipLaunchKernelGGL((solve_panel_kernel<8, 8>), dim3(1), dim3(kSolveThreads), 0, s, o);
+            else if (nb == 4)
+                hipLaunchKernelGGL((solve_panel_kernel<4, 16>), dim3(1), dim3(kSolveThreads), 0, s, o);
+            else
+                hipLaunchKernelGGL((solve_panel_kernel<2, 16, kTallThreads>), dim3(1), dim3(kTallThreads), 0, s, o);
+            update(kk + o.nb, ce);               // the outer panel's later columns
+        }
+        o.kk = k0;
+        o.nb = o.nbo;
+        const unsigned col_groups = (unsigned)((ld - ce + kSwapCols - 1) / kSwapCols);   // >= 1: right-hand sides
         hipLaunchKernelGGL(solve_swap_trsm_kernel, dim3(col_groups), dim3(kSwapThreads), 0, s, o);
-        if (c0 < m)
-            hipLaunchKernelGGL(solve_update_kernel,
-                               dim3((unsigned)((ld - c0 + kUpdTile - 1) / kUpdTile),
-                                    (unsigned)((m - c0 + kUpdTile - 1) / kUpdTile)),
-                               dim3(kUpdThreads), 0, s, o);
+        update(ce, ld);
     }
-    hipLaunchKernelGGL(solve_back_kernel, dim3(1), dim3(kSolveThreads), 0, s, a);
+    BackArgs b;
+    b.A = work;
+    b.x = x;
+    b.m = m;
+    b.n_rhs = n_rhs;
+    for (b.hi = m; b.hi > 0; b.hi = b.lo) {
+        b.lo = std::max(0, b.hi - kBackRows);
+        hipLaunchKernelGGL(solve_back_block_kernel, dim3((unsigned)((n_rhs + kBackRhs - 1) / kBackRhs)), dim3(kSolveThreads),
+                           0, s, b);
+        if (b.lo > 0)
+            hipLaunchKernelGGL(solve_back_above_kernel, dim3((unsigned)((b.lo + kAboveRows - 1) / kAboveRows), (unsigned)n_rhs),
+                               dim3(256), 0, s, b);
+    }
     return hipGetLastError();
 }
 
