@@ -30,8 +30,7 @@
 // N' is an integer; here it is evaluated as N' = c (c - 2(a+b-1)) + a(a-2) + b(b-2)
 // with one fused multiply-add, rounded once while a(a-2) + b(b-2) < 2^53
 // (lmax <= 8000); beyond, that sum is not exact and N' cancels against it when
-// l1 << l2, so N' = t^2 - (2ab+1), t = c - (a+b-1), with 2ab+1 split exactly
-// into two doubles (see strip_fp64_kernel).  The
+// l1 << l2, so N' is a product of two exact factors and a rest (n_shift).  The
 // "(2,-2,0) recurrence" is thus an integer update of c along the strip.  The
 // three kernels then are
 //
@@ -220,8 +219,8 @@ struct Win {
 enum : int { kModeTT = 0, kModePol = 1, kModeEB = 2, kModePolEE = 3, kModeEE = 4 };
 
 // WIDE (lmax > kNarrowLmax): a(a-2) + b(b-2) exceeds 2^53 and N' cancels
-// against it when l1 << l2, so N' is taken as t^2 - (2ab + 1) with t exact and
-// 2ab + 1 = beta_hi + beta_lo split exactly: one more operation per term.
+// against it when l1 << l2, so N' is taken as a product of two exact factors and
+// an exact rest (n_shift, n_rest): rounded once too, one more operation per step.
 // (kNarrowLmax: strip_params.hpp)
 
 template <int R, int MODE, bool WIDE>
@@ -250,24 +249,23 @@ strip_fp64_kernel(StripArgs a) {
     const int l1_0 = A + R * lane;
 
     // even L: N' = c (c - gam2) + kap, every piece exact while lmax <= kNarrowLmax;
-    //   WIDE: N' = t^2 - kap - blo, t = c - gam2, gam2 = a + b - 1, kap + blo = 2ab + 1.
+    //   WIDE: N' = (c - gam2)(c - ed) + kap, the shifted product of n_shift and n_rest, exact as well.
     // EB: gam2 = sig(sig+1), kap = mu.
-    double tt[R], te[R], ee[R], gam2[R], kap[R], blo[R], gw[R], hw[R];
+    double tt[R], te[R], ee[R], gam2[R], kap[R], gw[R], hw[R];
+    // WIDE: the item's shift, from its middle row
+    const long long shift = WIDE ? n_shift(2LL * max(A + B / 2, 0) + d, d) : 0;
+    const double ed = (double)((long long)d * d - 2 + shift);
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         tt[j] = te[j] = ee[j] = 0.0;
-        blo[j] = 0.0;
         const long long l1 = l1_0 + j, l2 = l1 + d;
         if (EB) {
             const long long sg = l1 + l2 + 1, tau = sg + 1;
             gam2[j] = (double)(sg * (sg + 1));
             kap[j] = (double)(2 * (l1 + 2) * (l2 + 2) - tau * (tau + 1));
         } else if (WIDE) {
-            const long long aa = l1 * (l1 + 1), bb = l2 * (l2 + 1);
-            const long long beta = 2 * aa * bb + 1;
-            gam2[j] = (double)(aa + bb - 1);
-            kap[j] = (double)beta;
-            blo[j] = (double)(beta - (long long)kap[j]);
+            gam2[j] = (double)((l1 + l2 + 1) * (l1 + l2 + 1) - 1 - shift);
+            kap[j] = (double)n_rest(l1 + l2, d, shift);
         } else {
             const long long aa = l1 * (l1 + 1), bb = l2 * (l2 + 1);
             gam2[j] = (double)(2 * (aa + bb - 1));
@@ -379,15 +377,14 @@ strip_fp64_kernel(StripArgs a) {
                         // (sig(sig+1) - c) (c + mu)^2, each factor an exact integer
                         const double f1 = gam2[j] - uu.w;
                         const double f3 = uu.w + kap[j];
-                        tt[j] = __builtin_fma(uu.x, P * ((f1 * f3) * f3), tt[j]);
+                        tt[j] = __builtin_fma(uu.x, ((P * f1) * f3) * f3, tt[j]);
                         continue;
                     }
                     if (TTS) tt[j] = __builtin_fma(uu.x, P, tt[j]);
                     if (POL) {
                         double N;
                         if (WIDE) {
-                            const double t = uu.w - gam2[j];
-                            N = __builtin_fma(t, t, -kap[j]) - blo[j];
+                            N = __builtin_fma(uu.w - gam2[j], uu.w - ed, kap[j]);
                         } else {
                             const double dc = uu.w - gam2[j];
                             N = __builtin_fma(uu.w, dc, kap[j]);
@@ -1068,14 +1065,16 @@ strip_fp64_masks_kernel(StripArgs a) {
     const int lane = threadIdx.x;
     const int l1_0 = A + R * lane;
 
-    // N' per row as in strip_fp64_kernel (narrow: c (c - gam2) + kap; WIDE: t^2 - kap - blo);
+    // N' per row as in strip_fp64_kernel (narrow: c (c - gam2) + kap; WIDE: (c - gam2)(c - ed) + kap);
     // EB: gam2 = sig(sig+1), kap = mu
-    double tt[R][M], te[R][M], ee[R][M], gam2[R], kap[R], blo[R], gw[R], hw[R];
+    double tt[R][M], te[R][M], ee[R][M], gam2[R], kap[R], gw[R], hw[R];
+    // WIDE: the item's shift, from its middle row
+    const long long shift = WIDE ? n_shift(2LL * max(A + B / 2, 0) + d, d) : 0;
+    const double ed = (double)((long long)d * d - 2 + shift);
 #pragma unroll
     for (int j = 0; j < R; ++j) {
 #pragma unroll
         for (int m = 0; m < M; ++m) tt[j][m] = te[j][m] = ee[j][m] = 0.0;
-        blo[j] = 0.0;
         const long long l1 = l1_0 + j, l2 = l1 + d;
         const long long aa = l1 * (l1 + 1), bb = l2 * (l2 + 1);
         if (EB) {
@@ -1083,10 +1082,8 @@ strip_fp64_masks_kernel(StripArgs a) {
             gam2[j] = (double)(sg * (sg + 1));
             kap[j] = (double)(2 * (l1 + 2) * (l2 + 2) - tau * (tau + 1));
         } else if (WIDE) {
-            const long long beta = 2 * aa * bb + 1;
-            gam2[j] = (double)(aa + bb - 1);
-            kap[j] = (double)beta;
-            blo[j] = (double)(beta - (long long)kap[j]);
+            gam2[j] = (double)((l1 + l2 + 1) * (l1 + l2 + 1) - 1 - shift);
+            kap[j] = (double)n_rest(l1 + l2, d, shift);
         } else {
             gam2[j] = (double)(2 * (aa + bb - 1));
             kap[j] = (double)(aa * (aa - 2) + bb * (bb - 2));
@@ -1166,7 +1163,7 @@ strip_fp64_masks_kernel(StripArgs a) {
                         // (sig(sig+1) - c) (c + mu)^2, each factor an exact integer
                         const double f1 = gam2[j] - c;
                         const double f3 = c + kap[j];
-                        const double e = P * ((f1 * f3) * f3);
+                        const double e = ((P * f1) * f3) * f3;
 #pragma unroll
                         for (int m = 0; m < M; ++m) tt[j][m] = __builtin_fma(uf[m], e, tt[j][m]);
                         continue;
@@ -1177,8 +1174,7 @@ strip_fp64_masks_kernel(StripArgs a) {
                     if (POL) {
                         double N;
                         if (WIDE) {
-                            const double t = c - gam2[j];
-                            N = __builtin_fma(t, t, -kap[j]) - blo[j];
+                            N = __builtin_fma(c - gam2[j], c - ed, kap[j]);
                         } else {
                             const double dc = c - gam2[j];
                             N = __builtin_fma(c, dc, kap[j]);
@@ -1323,6 +1319,16 @@ hipError_t launch_strip(const couple_ctx* ctx, int lmax, int mode, int precision
     a.l3_lo = l3_lo;
     a.l3_hi = l3_hi;
     a.band = a.dmax < lmax ? 1 : 0;
+    // float64 over every diagonal: the tile kernels from the sizes where they are
+    // ahead (same bits).  A band keeps the strips, whose diagonals stop exactly at the
+    // band's end.
+    const int tile_min = mode == kStripTT      ? 0
+                         : mode == kStripPol   ? kTileMinPol
+                         : mode == kStripPolEE ? kTileMinPolEE
+                         : mode == kStripEE    ? kTileMinEE
+                                               : kTileMinEB;
+    if (precision == COUPLE_FP64 && !a.band && lmax >= tile_min)
+        return launch_tile_fp64(ctx, lmax, mode, l3_lo, l3_hi, s);
     if (mode == kStripTT) {
         constexpr int RT = kStripRTT;
         const long long n_tt = count_items(lmax, a.dmax, kWave * RT, a.band != 0);

@@ -62,9 +62,28 @@ constexpr int kStripChunkF64Masks = 128;
 // 254 (2 l3 + 255) < 2^24 for l3 <= 2 x 16384, hence exact in float32.
 constexpr int kStripRebase = 128;
 
-// Above this lmax the float64 kernels form N' in the WIDE way (two more
-// exact pieces per row), since a(a-2) + b(b-2) no longer fits 2^53.
+// Above this lmax the float64 strip kernels form N' by n_shift and n_rest below
+// (one more operation per step), since a(a-2) + b(b-2) no longer fits 2^53.
 constexpr int kNarrowLmax = 8000;
+
+// The float64 whole-triangle kernels (tile.hip) against the diagonal strips, per
+// strip mode, in us per call of couple_matrix (strips / tiles):
+//   lmax                        1000       1200       1500       2000        3000
+//   TT                          -          98 / 52    130 / 70   227 / 110   584 / 276
+//   TT + TE + EE                119 / 147  168 / 179  261 / 248  511 / 443   1526 / 1271
+//   TT + EE                     99 / 104   138 / 132  220 / 186  434 / 348   -
+//   EE                          79 / 99    114 / 118  179 / 162  369 / 285   1090 / 797
+//   EB                          89 / 87    127 / 102  200 / 153  407 / 268   1220 / 748
+// Small triangles leave the tiles' longer patches without enough waves; TT's stay
+// ahead at every size.
+constexpr int kTileMinPol = 1400, kTileMinPolEE = 1150, kTileMinEE = 1250, kTileMinEB = 1000;
+// lmax from which a thread takes 4 x 2 and 4 x 4 (s, d) values instead of 2 x 2 (TT +
+// TE + EE at 2000 / 2500 / 3000: 443 / 804 / 1358 us with 2 x 2, 502 / 788 / 1277 with
+// 4 x 2, 643 / 935 / 1271 with 4 x 4), and a wave of the TT kernel 2 x 2 and 4 x 2 MFMA
+// tiles instead of one (2000 / 3000 / 10^4: 110 / 286 / 8499 us with one, 153 / 276 / 6785
+// with 2 x 2, 209 / 361 / 6652 with 4 x 2).
+constexpr int kTilePolMid = 2400, kTilePolBig = 2900;
+constexpr int kTileTTMid = 2700, kTileTTBig = 6000;
 
 // Zero guard band around the device copies of g(p) and 1/((2p+1)g(p)).
 constexpr int kTablePad = 64;
@@ -76,6 +95,23 @@ __host__ __device__ inline long long diag_offset(int lmax, int d) {
 }
 __host__ __device__ inline long long tri_size(int lmax) {
     return (long long)(lmax + 1) * (lmax + 2) / 2;
+}
+
+// The (-2 2 0) polynomial as a product and a rest (tile.hip): with s = l1 + l2, d =
+// l2 - l1 and any integer a,
+//     N' = (c - (s+1)^2 + 1 + a)(c - d^2 + 2 - a) + rest(s, d, a).
+// For a near (1 - 1/sqrt 2)/2 ((s+1)^2 - d^2) the rest nearly vanishes, and over a
+// patch of 512 rows of a diagonal, or 128 values of s and of d, around the (s, d)
+// that a is taken from it stays below 2^52 up to lmax = 16384 (with a = 0 it passes
+// 2^53 beyond lmax = 8000): exact in float64, so that N' is one fused
+// multiply-add, rounded once.
+__device__ inline long long n_shift(long long s, long long d) {
+    const long long x = (s + 1) * (s + 1) - d * d;
+    return x > 0 ? (long long)(0.14644660940672624 * (double)x) : 0;
+}
+__device__ inline long long n_rest(long long s, long long d, long long a) {
+    const long long S = (s + 1) * (s + 1), D = d * d;
+    return ((S - D) * (S - D) + 6 * S - 2 * D - 7) / 8 - a * (S - D + 1) + a * a;
 }
 
 // Strip kernel modes: Xi_TT; Xi_TT, Xi_TE, Xi_EE (even L); Xi_EB (odd L).
