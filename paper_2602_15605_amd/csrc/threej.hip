@@ -17,22 +17,36 @@
 //     Y' = (l1, l2+1, l3; 0 0 0), sig = l1 + l2 + 1, tau = sig + 1,
 //     mu = 2 (l1+2)(l2+2) - tau(tau+1), d = l2 - l1;
 //   zero for l1 or l2 < 2.
-// Every integer factor is exact in int64; the only roundings are the table
-// values, the products and one square root, so there is no cancellation.
+// Every integer factor is exact (or, for N', one rounding of an exact value); the
+// other roundings are the table values, the products and one square root, so there is
+// no cancellation.
 //
-// The second kernel below extends this to (l1 l2 l3; m1 m2 m3) with small
+// The family kernels below extend this to (l1 l2 l3; m1 m2 m3) with small
 // magnetic numbers, (1 1 -2) and (2 2 -4) among them.
 //
-// One 256-thread work-group per (l1, l2) pair, threads over l3.  The pairs
-// are read from device memory, so the kernel itself checks them: a pair
+// One 256-thread work-group per (l1, l2) pair and piece of its row, threads over
+// l3.  The pairs are read from device memory, so the kernel itself checks them: a pair
 // outside [0, lmax_max] gives a row of NaN and reads no table.
+#include <algorithm>
+#include <type_traits>
+
 #include "couple_internal.hpp"
 
 namespace couple {
 namespace {
 
 constexpr int kThreejThreads = 256;
-constexpr int kThreejBatch = 4;
+constexpr int kThreejBatch = 2;
+// Entries of a row per block.  One block per row left the longest rows running alone at
+// the end (on average half the waves that fit): with the kernels below 2000 rows at lmax
+// 6000 took 64 us (m = 1) and 75 us ((2 2 -4)), with these pieces 37 and 54 us (1024
+// entries: 52 and 79 us, the row's setup weighs more; 8192: 58 and 65 us).  Plain stores:
+// past the caches (nontemporal) the same rows took 56 and 64 us.
+constexpr int kThreejPiece = 2048;
+
+inline dim3 piece_grid(int n_pairs, long long stride) {
+    return dim3((unsigned)n_pairs, (unsigned)std::min((stride + kThreejPiece - 1) / kThreejPiece, 1024LL));
+}
 
 struct ThreejArgs {
     const double* g;             // g(p), p = 0 .. lmax_max
@@ -46,41 +60,34 @@ struct ThreejArgs {
     int m;
 };
 
-// (j1 j2 j3; 0 0 0) with the triangle rule; every index stays inside the
-// tables when j1, j2 <= lmax_max + 1 and j3 <= j1 + j2 - 1 or j1, j2 <= lmax_max.
-__device__ inline double x000(const ThreejArgs& a, long long j1, long long j2, long long j3) {
-    const long long L = j1 + j2 + j3;
-    if (L & 1) return 0.0;
-    if (j3 < (j1 > j2 ? j1 - j2 : j2 - j1) || j3 > j1 + j2) return 0.0;
-    const long long P = L / 2;
-    const double v = sqrt(a.g[P - j1] * a.g[P - j2] * a.g[P - j3] * a.h[P]);
-    return (P & 1) ? -v : v;
+// Zeros in entries i .. end - 1 of a row, 16 bytes per store.
+__device__ inline void put_zeros(double* row, long long i, long long end) {
+    typedef double d2v __attribute__((ext_vector_type(2)));
+    if (i < end && (reinterpret_cast<uintptr_t>(row + i) & 15)) {
+        if (threadIdx.x == 0) row[i] = 0.0;
+        ++i;
+    }
+    const long long pairs = end > i ? (end - i) / 2 : 0;
+    d2v* out = reinterpret_cast<d2v*>(row + i);
+    for (long long q = threadIdx.x; q < pairs; q += kThreejThreads)
+        out[q] = d2v{0.0, 0.0};
+    if (threadIdx.x == 0 && i + 2 * pairs < end) row[end - 1] = 0.0;
 }
 
-// m = 1, 2, with rowf from row_factor.  Both parities share one (0 0 0)
-// evaluation: (l1 l2 l3) for even L and (l1, l2+1, l3) for odd L, whose total
-// is then even.  Neighbouring l3 alternate in parity, so the two factors are
-// both formed and one is selected per lane, which keeps the wave on a single
-// path.  The factor of the parity not taken can be the root of a negative
-// number; it is discarded.
-__device__ inline double symbol(const ThreejArgs& a, long long l1, long long l2, long long l3, double rowf) {
-    const long long L = l1 + l2 + l3;
-    const long long odd = L & 1;
-    const double x = x000(a, l1, l2 + odd, l3);
-    const long long A = l1 * (l1 + 1), B = l2 * (l2 + 1), C = l3 * (l3 + 1);
-    if (a.m == 1) {
-        if (l1 < 1 || l2 < 1) return 0.0;
-        const double num = (double)((L + 2) * (L - 2 * l3 + 1)) * (double)((L - 2 * l1 + 1) * (L - 2 * l2));
-        const double f = odd ? sqrt(num) : (double)(A + B - C);
-        return f * rowf * x;
+// Runs `entries(lo, hi)` for the pieces of this block's row that hold some of its n
+// symbols, and writes NaN (a degree out of range) or zeros elsewhere.  Pieces start at
+// even entries.
+template <class Entries>
+__device__ inline void each_piece(double* row, long long n, long long stride, bool nan, Entries entries) {
+    for (long long lo = (long long)blockIdx.y * kThreejPiece; lo < stride; lo += (long long)gridDim.y * kThreejPiece) {
+        const long long end = min(lo + kThreejPiece, stride), hi = min(n, end);
+        if (nan) {
+            for (long long i = lo + threadIdx.x; i < end; i += kThreejThreads) row[i] = __builtin_nan("");
+            continue;
+        }
+        put_zeros(row, max(lo, hi), end);
+        if (lo < hi) entries((int)lo, (int)hi);
     }
-    if (l1 < 2 || l2 < 2) return 0.0;
-    const long long np = C * (C - 2 * (A + B - 1)) + A * (A - 2) + B * (B - 2);
-    const long long sg = l1 + l2 + 1, tau = sg + 1, d = l2 - l1;
-    const long long mu = 2 * (l1 + 2) * (l2 + 2) - tau * (tau + 1);
-    const long long f1 = sg * (sg + 1) - C, f2 = C - d * (d + 1);
-    const double f = odd ? -(double)(C + mu) * sqrt((double)f1 * (double)f2) : (double)np;
-    return x * f * rowf;
 }
 
 // The factor shared by a whole row: m = 1: -1 / (2 sqrt(a b)); m = 2: c_l1 c_l2 / 2.
@@ -95,47 +102,90 @@ __device__ inline double row_factor(const ThreejArgs& a, long long l1, long long
 // L vanish; a row starts at L = 2 max(l1, l2), so its even entries are the
 // even-L ones, and each thread takes a pair of entries: it evaluates the even
 // one and writes a zero beside it.
+//
+// m = 1, 2: a thread's entries lie an even number apart, so all of them have one
+// parity of L and it forms that parity's factor only.  Both parities need one
+// (0 0 0) value, (l1 l2 l3) for even L and (l1, l2+1, l3) for odd L, whose total is
+// then even; with p1, p2, p3 and P its halved combinations the factors are
+//   m = 1 even: (a + b - c);   odd: the root of (L+2)(L-2 l3+1)(L-2 l1+1)(L-2 l2);
+//   m = 2 even: N' (n_shift and n_rest of the row: one fused multiply-add);
+//         odd: -(c + mu) times the root of (sig(sig+1) - c)(c - d(d+1)),
+// the roots taken together with the (0 0 0) value's.  Every integer below is
+// exact in float64.  What bounds it: about 120 instructions per symbol, most of
+// them the root; with 64-bit integers, both parities' factors and two roots per
+// symbol 2000 rows at lmax 6000 took 57 us, now 37 us (115 MB of results and 77 MB of
+// zeros: 5.2 TB/s); 200 rows at lmax 16000 67 us, now 16 us.
 __global__ void __launch_bounds__(kThreejThreads) threej_rows_kernel(ThreejArgs a) {
     const long long p = blockIdx.x;
     const int l1 = a.l1[p], l2 = a.l2[p];
     double* row = a.out + p * a.stride;
-    if (l1 < 0 || l2 < 0 || l1 > a.lmax_max || l2 > a.lmax_max) {
-        for (long long i = threadIdx.x; i < a.stride; i += kThreejThreads) row[i] = __builtin_nan("");
+    const bool nan = l1 < 0 || l2 < 0 || l1 > a.lmax_max || l2 > a.lmax_max;
+    const int jmin = l1 > l2 ? l1 - l2 : l2 - l1;
+    if (nan || min(l1, l2) < a.m) {           // a selection rule |m| <= l fails: zeros
+        each_piece(row, 0, a.stride, nan, [](int, int) {});
         return;
     }
-    const long long jmin = l1 > l2 ? l1 - l2 : l2 - l1;
-    const long long n = (long long)l1 + l2 - jmin + 1;
+    const int n = l1 + l2 - jmin + 1;
     if (a.m == 0) {
-        for (long long q0 = threadIdx.x; 2 * q0 < a.stride; q0 += (long long)kThreejThreads * kThreejBatch) {
-            double v[kThreejBatch];
+        each_piece(row, n, a.stride, false, [&](int lo, int hi) {
+            for (int q0 = lo + 2 * threadIdx.x; q0 < hi; q0 += 2 * kThreejThreads * kThreejBatch) {
+                double v[kThreejBatch];
 #pragma unroll
-            for (int q = 0; q < kThreejBatch; ++q) {
-                const long long i = 2 * (q0 + (long long)q * kThreejThreads);
-                v[q] = i < n ? x000(a, l1, l2, jmin + i) : 0.0;
-            }
+                for (int q = 0; q < kThreejBatch; ++q) {
+                    const int i = min(q0 + 2 * q * kThreejThreads, (hi - 1) & ~1);
+                    const int P = (l1 + l2 + jmin + i) / 2;
+                    const double r = sqrt(a.g[P - l1] * a.g[P - l2] * a.g[P - jmin - i] * a.h[P]);
+                    v[q] = (P & 1) ? -r : r;
+                }
 #pragma unroll
-            for (int q = 0; q < kThreejBatch; ++q) {
-                const long long i = 2 * (q0 + (long long)q * kThreejThreads);
-                if (i < a.stride) row[i] = v[q];
-                if (i + 1 < a.stride) row[i + 1] = 0.0;
+                for (int q = 0; q < kThreejBatch; ++q) {
+                    const int i = q0 + 2 * q * kThreejThreads;
+                    if (i < hi) row[i] = v[q];
+                    if (i + 1 < hi) row[i + 1] = 0.0;
+                }
             }
-        }
+        });
         return;
     }
     const double rowf = row_factor(a, l1, l2);
-    for (long long i0 = threadIdx.x; i0 < a.stride; i0 += (long long)kThreejThreads * kThreejBatch) {
-        double v[kThreejBatch];
+    const int odd = (l1 + l2 + jmin + (int)threadIdx.x) & 1;
+    const double A = (double)l1 * (l1 + 1), B = (double)l2 * (l2 + 1);
+    // m = 2, even L: N' = (c - es)(c - ed) + rest; odd L: sig(sig+1), mu, d(d+1)
+    const long long s = (long long)l1 + l2, d = jmin, sh = n_shift(s, d);
+    const double es = (double)((s + 1) * (s + 1) - 1 - sh), ed = (double)(d * d - 2 + sh), rest = (double)n_rest(s, d, sh);
+    const long long dd = (long long)l2 - l1;
+    const double s1 = (double)((s + 1) * (s + 2)), d1 = (double)(dd * (dd + 1));
+    const double mu = (double)(2LL * (l1 + 2) * (l2 + 2) - (s + 2) * (s + 3));
+    each_piece(row, n, a.stride, false, [&](int lo, int hi) {
+        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += kThreejThreads * kThreejBatch) {
+            double v[kThreejBatch];
 #pragma unroll
-        for (int q = 0; q < kThreejBatch; ++q) {
-            const long long i = i0 + (long long)q * kThreejThreads;
-            v[q] = i < n ? symbol(a, l1, l2, jmin + i, rowf) : 0.0;
-        }
+            for (int q = 0; q < kThreejBatch; ++q) {
+                // entries past the piece repeat its last one of this parity, unstored
+                const int i = min(i0 + q * kThreejThreads, hi - 1 - ((hi - 1 - i0) & 1));
+                const int l3 = jmin + i, L = l1 + l2 + l3;
+                // (l1, l2 + odd, l3; 0 0 0)^2: odd L has |l1 - l2 - 1| <= l3 < l1 + l2
+                const int P = (L + odd) / 2;
+                double x = a.g[P - l1] * a.g[P - l2 - odd] * a.g[P - l3] * a.h[P];
+                const double c = (double)l3 * (l3 + 1);
+                double f;
+                if (a.m == 1) {
+                    f = odd ? 1.0 : A + B - c;
+                    if (odd) x *= ((double)(L + 2) * (double)(L - 2 * l3 + 1)) * ((double)(L - 2 * l1 + 1) * (double)(L - 2 * l2));
+                } else {
+                    f = odd ? -(c + mu) : __builtin_fma(c - es, c - ed, rest);
+                    if (odd) x *= (s1 - c) * (c - d1);
+                }
+                const double r = sqrt(x);
+                v[q] = ((P & 1) ? -r : r) * f * rowf;
+            }
 #pragma unroll
-        for (int q = 0; q < kThreejBatch; ++q) {
-            const long long i = i0 + (long long)q * kThreejThreads;
-            if (i < a.stride) row[i] = v[q];
+            for (int q = 0; q < kThreejBatch; ++q) {
+                const int i = i0 + q * kThreejThreads;
+                if (i < hi) row[i] = v[q];
+            }
         }
-    }
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -255,30 +305,107 @@ __device__ inline double family_symbol(const FamilyArgs& f, long long l1, long l
     return v;
 }
 
+// The general kernel: rows whose l3 is not the column z.
 template <int AB>
 __global__ void __launch_bounds__(kThreejThreads) threej_family_kernel(FamilyArgs f) {
     const long long p = blockIdx.x;
     const int l1 = f.l1[p], l2 = f.l2[p];
     double* row = f.out + p * f.stride;
-    if (l1 < 0 || l2 < 0 || l1 > f.lmax_max || l2 > f.lmax_max) {
-        for (long long i = threadIdx.x; i < f.stride; i += kThreejThreads) row[i] = __builtin_nan("");
+    const bool nan = l1 < 0 || l2 < 0 || l1 > f.lmax_max || l2 > f.lmax_max;
+    const long long jmin = l1 > l2 ? l1 - l2 : l2 - l1;
+    each_piece(row, nan ? 0 : (long long)l1 + l2 - jmin + 1, f.stride, nan, [&](int lo, int hi) {
+        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += kThreejThreads * kThreejBatch) {
+            double v[kThreejBatch];
+#pragma unroll
+            for (int q = 0; q < kThreejBatch; ++q) {
+                const int i = i0 + q * kThreejThreads;
+                v[q] = i < hi ? family_symbol<AB>(f, l1, l2, jmin + i) : 0.0;
+            }
+#pragma unroll
+            for (int q = 0; q < kThreejBatch; ++q) {
+                const int i = i0 + q * kThreejThreads;
+                if (i < hi) row[i] = v[q];
+            }
+        }
+    });
+}
+
+// v c modulo 2^128, from four 32-bit products.
+__device__ inline unsigned __int128 mul_u32(unsigned __int128 v, unsigned c) {
+    const unsigned long long a0 = (unsigned long long)(unsigned)v * c;
+    const unsigned long long a1 = (unsigned long long)(unsigned)(v >> 32) * c + (a0 >> 32);
+    const unsigned long long a2 = (unsigned long long)(unsigned)(v >> 64) * c + (a1 >> 32);
+    const unsigned a3 = (unsigned)(v >> 96) * c + (unsigned)(a2 >> 32);
+    return (unsigned __int128)(a1 << 32 | (unsigned)a0) | (unsigned __int128)((unsigned long long)a3 << 32 | (unsigned)a2) << 64;
+}
+
+// Rows with l3 = z (rot = 0: (1 1 -2), (2 2 -4) and their m-flips among them).
+// Along such a row A and B are fixed and N_ab is a quadratic in C, so its three
+// coefficients are formed once per row and a symbol takes two 128 x 32-bit
+// products, exact as before (|N| < 2^118, every partial sum below 2^127 and
+// wrapping harmless in any case).  A thread's entries lie an even number apart, so
+// all of them have one parity of L and it evaluates that parity's polynomial only;
+// the two roots become one, of the table product over D^2.
+// What bounds it: about 150 instructions per symbol.  2000 rows of (2 2 -4) at lmax 6000
+// take 54 us, with the full 128-bit polynomials of both parities and two roots per
+// symbol 131 us; (1 1 -2) 43 us, before 78 us.
+template <int AB>
+__global__ void __launch_bounds__(kThreejThreads) threej_family_row_kernel(FamilyArgs f) {
+    constexpr int a = AB / 3, b = AB % 3;
+    const long long p = blockIdx.x;
+    const int l1 = f.l1[p], l2 = f.l2[p];
+    double* row = f.out + p * f.stride;
+    const bool nan = l1 < 0 || l2 < 0 || l1 > f.lmax_max || l2 > f.lmax_max;
+    if (nan || l1 < a || l2 < b) {
+        each_piece(row, 0, f.stride, nan, [](int, int) {});
         return;
     }
-    const long long jmin = l1 > l2 ? l1 - l2 : l2 - l1;
-    const long long n = (long long)l1 + l2 - jmin + 1;
-    for (long long i0 = threadIdx.x; i0 < f.stride; i0 += (long long)kThreejThreads * kThreejBatch) {
-        double v[kThreejBatch];
-#pragma unroll
-        for (int q = 0; q < kThreejBatch; ++q) {
-            const long long i = i0 + (long long)q * kThreejThreads;
-            v[q] = i < n ? family_symbol<AB>(f, l1, l2, jmin + i) : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < kThreejBatch; ++q) {
-            const long long i = i0 + (long long)q * kThreejThreads;
-            if (i < f.stride) row[i] = v[q];
-        }
+    const int jmin = l1 > l2 ? l1 - l2 : l2 - l1, n = l1 + l2 - jmin + 1;
+    const long long A = (long long)l1 * (l1 + 1), B = (long long)l2 * (l2 + 1);
+    const int odd = (l1 + l2 + jmin + (int)threadIdx.x) & 1;
+    // N(C) = (c2 C + c1) C + c0 from N(0), N(1) and N(-1) (the sums are even)
+    __int128 c0, c1, c2;
+    {
+        const __int128 e0 = family_numerator<AB>(0, A, B, 0), ep = family_numerator<AB>(0, A, B, 1),
+                       em = family_numerator<AB>(0, A, B, -1);
+        const __int128 o0 = family_numerator<AB>(1, A, B, 0), op = family_numerator<AB>(1, A, B, 1),
+                       om = family_numerator<AB>(1, A, B, -1);
+        c0 = odd ? o0 : e0;
+        c1 = odd ? (op - om) / 2 : (ep - em) / 2;
+        c2 = (odd ? (op + om) / 2 : (ep + em) / 2) - c0;
     }
+    double dab = 1.0;
+#pragma unroll
+    for (int k = 0; k < a; ++k) dab *= (double)(A - k * (k + 1));
+#pragma unroll
+    for (int k = 0; k < b; ++k) dab *= (double)(B - k * (k + 1));
+    each_piece(row, n, f.stride, false, [&](int lo, int hi) {
+        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += kThreejThreads * kThreejBatch) {
+            double v[kThreejBatch];
+#pragma unroll
+            for (int q = 0; q < kThreejBatch; ++q) {
+                const int i = min(i0 + q * kThreejThreads, hi - 1 - ((hi - 1 - i0) & 1));
+                const int l3 = jmin + i, L = l1 + l2 + l3, P = (L + 1) / 2;
+                const int p1 = P - l1, p2 = P - l2, p3 = P - l3;
+                const int C = l3 * (l3 + 1);
+                double base = f.g[p1] * f.g[p2] * f.g[p3] * f.h[P];
+                if (odd) base *= (8.0 * (double)p1 * (double)p2 * (double)p3) * (double)(L + 2);
+                double d2 = dab;
+#pragma unroll
+                for (int k = 0; k < a + b; ++k) d2 *= (double)(C - k * (k + 1));
+                const unsigned __int128 N =
+                    mul_u32(mul_u32((unsigned __int128)c2, (unsigned)C) + (unsigned __int128)c1, (unsigned)C) + (unsigned __int128)c0;
+                const double r = 0.5 * sqrt(base / d2) * i128_to_double((__int128)N);
+                const bool minus = ((P & 1) != 0) != (f.flip && odd);
+                v[q] = l3 < a + b ? 0.0 : (minus ? -r : r);
+            }
+#pragma unroll
+            for (int q = 0; q < kThreejBatch; ++q) {
+                const int i = i0 + q * kThreejThreads;
+                if (i < hi) row[i] = v[q];
+            }
+        }
+    });
 }
 
 }  // namespace
@@ -295,17 +422,24 @@ hipError_t launch_threej_family(const couple_ctx* ctx, int rot, int flip, int a,
     f.lmax_max = ctx->lmax_max;
     f.rot = rot;
     f.flip = flip;
-    const dim3 grid((unsigned)n_pairs), block(kThreejThreads);
+    const dim3 grid = piece_grid(n_pairs, stride), block(kThreejThreads);
+    auto launch = [&](auto ab) {
+        constexpr int AB = decltype(ab)::value;
+        if (rot == 0)
+            hipLaunchKernelGGL(threej_family_row_kernel<AB>, grid, block, 0, s, f);
+        else
+            hipLaunchKernelGGL(threej_family_kernel<AB>, grid, block, 0, s, f);
+    };
     switch (3 * a + b) {
-    case 0: hipLaunchKernelGGL(threej_family_kernel<0>, grid, block, 0, s, f); break;
-    case 1: hipLaunchKernelGGL(threej_family_kernel<1>, grid, block, 0, s, f); break;
-    case 2: hipLaunchKernelGGL(threej_family_kernel<2>, grid, block, 0, s, f); break;
-    case 3: hipLaunchKernelGGL(threej_family_kernel<3>, grid, block, 0, s, f); break;
-    case 4: hipLaunchKernelGGL(threej_family_kernel<4>, grid, block, 0, s, f); break;
-    case 5: hipLaunchKernelGGL(threej_family_kernel<5>, grid, block, 0, s, f); break;
-    case 6: hipLaunchKernelGGL(threej_family_kernel<6>, grid, block, 0, s, f); break;
-    case 7: hipLaunchKernelGGL(threej_family_kernel<7>, grid, block, 0, s, f); break;
-    case 8: hipLaunchKernelGGL(threej_family_kernel<8>, grid, block, 0, s, f); break;
+    case 0: launch(std::integral_constant<int, 0>()); break;
+    case 1: launch(std::integral_constant<int, 1>()); break;
+    case 2: launch(std::integral_constant<int, 2>()); break;
+    case 3: launch(std::integral_constant<int, 3>()); break;
+    case 4: launch(std::integral_constant<int, 4>()); break;
+    case 5: launch(std::integral_constant<int, 5>()); break;
+    case 6: launch(std::integral_constant<int, 6>()); break;
+    case 7: launch(std::integral_constant<int, 7>()); break;
+    case 8: launch(std::integral_constant<int, 8>()); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -323,7 +457,7 @@ hipError_t launch_threej_rows(const couple_ctx* ctx, int m, int n_pairs, const i
     a.stride = stride;
     a.lmax_max = ctx->lmax_max;
     a.m = m;
-    hipLaunchKernelGGL(threej_rows_kernel, dim3((unsigned)n_pairs), dim3(kThreejThreads), 0, s, a);
+    hipLaunchKernelGGL(threej_rows_kernel, piece_grid(n_pairs, stride), dim3(kThreejThreads), 0, s, a);
     return hipGetLastError();
 }
 
