@@ -21,9 +21,9 @@
 // the panel (RPT rows of NB columns, 64 doubles at most), so a column step
 // needs the pivot search and one broadcast row.  Per column, each wave finds its
 // largest entry (16-lane DPP maxima of the high words; the low words and the row
-// numbers only on ties), its owner leaves the row and 1/pivot in LDS, one
-// barrier, and every wave picks the winner among the waves' candidates; two LDS
-// buffers in turn need no second barrier.  Rows are not moved: a thread keeps
+// numbers only on ties) and leaves its row in LDS, one barrier, and every wave
+// picks the winner among the waves' candidates; two LDS buffers in turn need no
+// second barrier.  Rows are not moved: a thread keeps
 // the position its row has after the exchanges.
 //
 // Small systems (m < kMultiMin) run in one work-group (master_solve_kernel),
@@ -35,14 +35,19 @@
 //                             ones) and applies their exchanges and U12 to the
 //                             outer panel's other columns; a panel of fewer than
 //                             kOuterNB columns is followed by an update of the
-//                             outer panel's later columns;
+//                             outer panel's later columns; the other work-groups of
+//                             its launches do the update that the previous outer
+//                             panel left waiting (below);
 //   solve_swap_trsm_kernel    right of the outer panel, one thread per column:
 //                             the panel's row exchanges, composed into one
 //                             permutation of the touched rows, then
 //                             U12 = L11^-1 A12;
 //   solve_update_kernel       A22 -= L21 U12 in 64 x 64 tiles on the float64
 //                             matrix cores (v_mfma_f64_16x16x4: each entry is a
-//                             chain of fused multiply-adds in column order);
+//                             chain of fused multiply-adds in column order), for the
+//                             next outer panel's columns; the columns right of those
+//                             wait and are updated beside that panel's factorisation,
+//                             which keeps one compute unit busy and leaves 255;
 //   solve_back_block_kernel,  back substitution: one work-group solves a block of
 //   solve_back_above_kernel   kBackRows rows, then every row above it is updated.
 // The panel's pivots travel from the panel kernel to the swap kernel in the
@@ -166,15 +171,18 @@ __device__ inline bool plain_exponent(unsigned hi) { return (hi >> 20) - 23u <= 
 template <int NB>
 struct PivotLds {
     double blk[NB][NB + 2];       // row j of the factorised top block (L11 and U11), in the register order of step j
-    int4 key[2][kMostWaves];      // each wave's candidate: high and low word of |pivot|, row position
+    double cand[2][NB < 4 ? kMostWaves : kSolveWaves][NB + 2];   // each wave's candidate row
+    int4 key[2][kMostWaves];      // high and low word of its |pivot|, its position
     int piv[NB];                  // row exchanged with row j at step j (panel rows)
     int sing;                     // the panel met a zero pivot
 };
 
 // The rows of a panel that a thread holds: row threadIdx.x + q stride in a[q].
 // A row leaves when it becomes a pivot (step = its column; its live columns go
-// to PivotLds::blk and are 0 here from then on); step is -1 before that, and NB
-// where there is no row.  pos is the position of row q = 0, which only an
+// to PivotLds::blk); from then on it takes no part: in panels of 32 columns the
+// search and the multiplier skip it, in narrower ones, which have more rows than
+// columns per thread, its live columns are set to 0.  step is -1 before that, and
+// NB where there is no row.  pos is the position of row q = 0, which only an
 // exchange with one of the panel's first NB rows changes.  Other rows stay
 // where they are until they leave.
 template <int NB, int RPT>
@@ -192,9 +200,10 @@ template <int NB, int RPT, int GB, int J>
 __device__ __forceinline__ void factor_column(PanelRows<NB, RPT>& R, int jj, int live, int waves, PivotLds<NB>& S) {
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     // the wave's largest entry (high words, low words only on ties), its lane w
+    constexpr bool kSkip = NB == 32;          // rows that left are skipped, not zeroed
     double mx = 0.0;
 #pragma unroll
-    for (int q = 0; q < RPT; ++q) mx = fmax(mx, fabs(R.a[q][J]));
+    for (int q = 0; q < RPT; ++q) mx = fmax(mx, kSkip && R.step[q] >= 0 ? 0.0 : fabs(R.a[q][J]));
     const long long bits = __double_as_longlong(mx);
     const unsigned hi = (unsigned)(bits >> 32), lo = (unsigned)bits;
     unsigned kh = wave_max(hi);
@@ -230,9 +239,25 @@ __device__ __forceinline__ void factor_column(PanelRows<NB, RPT>& R, int jj, int
             }
         }
     }
-    bool mine = true;
+    // the wave's candidate row and its key
+    constexpr int buf = J & 1;
+    double* mine_row = S.cand[buf][wave];
+#pragma unroll
+    for (int q = 0; q < RPT; ++q)
+        if (q == wq) {
+            if (lane == w) {
+#pragma unroll
+                for (int g = 0; g < NB; g += GB) {
+                    if (g > 0 && g >= live) continue;
+#pragma unroll
+                    for (int c = g; c < g + GB; ++c) mine_row[c] = R.a[q][c];
+                }
+            }
+            // the branches stay apart: merged, they would index a in scratch
+            if (RPT > 1) asm volatile("; row %0" ::"s"(q));
+        }
+    int cw = 0;
     if (waves > 1) {
-        constexpr int buf = J & 1;
         if (lane == 0) S.key[buf][wave] = make_int4((int)kh, (int)kl, p, 0);
         __syncthreads();
         const int4 k = S.key[buf][lane < waves ? lane : 0];
@@ -251,16 +276,31 @@ __device__ __forceinline__ void factor_column(PanelRows<NB, RPT>& R, int jj, int
                 c = __ballot(on && key == best);
             }
         }
-        const int cw = __ffsll((long long)c) - 1;
-        mine = cw == wave;
+        cw = __ffsll((long long)c) - 1;
         kh = mh;
         kl = __builtin_amdgcn_readlane(k.y, cw);
         p = __builtin_amdgcn_readlane(k.z, cw);
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
-    // the pivot row leaves its registers
-    if (mine) {
-        if (lane == w) {
-            double* r = S.blk[jj];
+    const double* r = S.cand[buf][cw];
+    const double r0 = r[lane % (NB < 16 ? NB : 16)];
+    const double r1 = NB > 16 ? r[16 + lane % 16] : 0.0;
+    // the pivot row leaves
+    if (cw == wave) {
+        if (lane < (NB < 16 ? NB : 16)) {
+            S.blk[jj][lane] = r0;
+            if (NB > 16) S.blk[jj][16 + lane] = r1;
+        }
+        if (lane == 0) {
+            S.piv[jj] = p;
+            if ((kh | kl) == 0) S.sing = 1;
+        }
+        if (kSkip) {
+#pragma unroll
+            for (int q = 0; q < RPT; ++q) R.step[q] = q == wq && lane == w ? jj : R.step[q];
+        } else if (lane == w) {
 #pragma unroll
             for (int q = 0; q < RPT; ++q)
                 if (q == wq) {
@@ -268,17 +308,11 @@ __device__ __forceinline__ void factor_column(PanelRows<NB, RPT>& R, int jj, int
                     for (int g = 0; g < NB; g += GB) {
                         if (g > 0 && g >= live) continue;
 #pragma unroll
-                        for (int c = g; c < g + GB; ++c) {
-                            r[c] = R.a[q][c];
-                            R.a[q][c] = 0.0;
-                        }
+                        for (int c = g; c < g + GB; ++c) R.a[q][c] = 0.0;
                     }
                     R.step[q] = jj;
-                    // the branches stay apart: merged, they would index a in scratch
                     if (RPT > 1) asm volatile("; row %0" ::"s"(q));
                 }
-            S.piv[jj] = p;
-            if ((kh | kl) == 0) S.sing = 1;
         }
     }
     R.pos = R.pos == jj ? p : R.pos;
@@ -295,23 +329,14 @@ __device__ __forceinline__ void factor_column(PanelRows<NB, RPT>& R, int jj, int
 #pragma unroll
         for (int q = 0; q < RPT; ++q) l[q] = R.a[q][J] / apv;
     }
-    if (waves > 1) {
-        __syncthreads();
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
-    const double* r = S.blk[jj];
-    const double r0 = r[lane % (NB < 16 ? NB : 16)];
-    const double r1 = NB > 16 ? r[16 + lane % 16] : 0.0;
     const double pv = row16_bcast(r0, J);
     const long long sign = __double_as_longlong(pv) & (1LL << 63);
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         R.a[q][J] = __longlong_as_double(__double_as_longlong(l[q]) ^ sign);
-        l[q] = -R.a[q][J];
+        l[q] = kSkip && R.step[q] >= 0 ? 0.0 : -R.a[q][J];
     }
-    // the columns after jj, block by block (rows that left hold zeros)
+    // the columns after jj, block by block
 #pragma unroll
     for (int g = 0; g < NB; g += GB) {
         if (g > 0 && g >= live) continue;
@@ -345,13 +370,15 @@ __device__ __forceinline__ void factor_block(PanelRows<NB, RPT>& R, int j0, int 
 // Columns run in blocks of 8 through one copy of the code, the registers rotated
 // by a block after each (a copy per column would be 90 KB for 32 columns, more
 // than the instruction cache holds).  What bounds it: the dependent chain of a
-// column (search, two barriers with an LDS exchange each, then the update).
+// column (search, one LDS exchange with a barrier, then the update): 3000 clocks for
+// 8 waves of 2 x 32 or 8 x 8 entries per thread.
 template <int NB, int RPT>
 __device__ __forceinline__ void factor_rows(PanelRows<NB, RPT>& R, int nb, int waves, PivotLds<NB>& S) {
     constexpr int GB = NB < 8 ? NB : 8;
     if ((int)(threadIdx.x / kWave) >= waves) {
         if (waves > 1)
-            for (int j = 0; j < 2 * nb; ++j) __syncthreads();
+            for (int j = 0; j < nb; ++j) __syncthreads();
+        __syncthreads();
         return;
     }
 #pragma unroll 1
@@ -370,6 +397,7 @@ __device__ __forceinline__ void factor_rows(PanelRows<NB, RPT>& R, int nb, int w
             }
         }
     }
+    __syncthreads();
 }
 
 // The factorised panel: put(r, c, v) for every entry that it holds, row
@@ -457,6 +485,18 @@ __device__ inline void compose_moves(const PivotLds<NB>& S, int nb, int* src, in
     if (l >= nb && l < n && from < nb) dst[from] = at;
 }
 
+// u = L^-1 u for a unit lower triangle: row j, column i of it at lp[i ls + j], times sign.
+template <int NB>
+__device__ __forceinline__ void solve_lower(const double* lp, int ls, double sign, double (&u)[NB]) {
+    int ofs = 0;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        asm volatile("" : "+v"(ofs), "+v"(u[i]));   // a column of L is read when its turn comes, not before
+#pragma unroll
+        for (int j = i + 1; j < NB; ++j) u[j] = __builtin_fma(sign * lp[ofs + i * ls + j], u[i], u[j]);
+    }
+}
+
 // Column Ac of the matrix (from the panel's first row on): the panel's
 // exchanges, then with `solve` U12 = L11^-1 A12, L11 read as lp[i ls + j] (row
 // j, column i) times sign.  Every touched row is loaded before any is stored;
@@ -478,15 +518,7 @@ __device__ inline void move_and_solve(double* Ac, int nb, bool moved, const int*
 #pragma unroll
         for (int i = 0; i < NB; ++i) u[i] = Ac[min(i, nb - 1)];
     }
-    if (solve) {
-        int ofs = 0;
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            asm volatile("" : "+v"(ofs), "+v"(u[i]));   // a column of L11 is read when its turn comes, not before
-#pragma unroll
-            for (int j = i + 1; j < NB; ++j) u[j] = __builtin_fma(sign * lp[ofs + i * ls + j], u[i], u[j]);
-        }
-    }
+    if (solve) solve_lower<NB>(lp, ls, sign, u);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
         if (i < nb) Ac[i] = u[i];
@@ -642,7 +674,6 @@ __device__ __forceinline__ void one_panel(double* A, long long m, int k0, int mr
     PanelRows<NB, RPT> R;
     load_rows<NB, RPT>(R, A, m, k0, mr, nb, waves);
     factor_rows<NB, RPT>(R, nb, waves, L.p);
-    if (waves == 1) __syncthreads();         // blk and piv for every wave (the last column's barrier otherwise)
     if (L.p.sing) return;                    // positions hold nothing of use then
     put_rows(R, L.p, nb, [&](int r, int c, double v) {
         L.l[c][r] = -v;
@@ -701,17 +732,50 @@ __global__ void __launch_bounds__(kSolveThreads) master_solve_kernel(SolveArgs a
         const bool moved = S.e.moved != 0;
         for (int c0 = k0 + nb; c0 < ld; c0 += kOneCols) {
             const int w = min(kOneCols, ld - c0);
-            if (t < kOneCols) {
+            // the exchanges, the top block into S.e.u: a wave takes 8 x 8 entries at a time, so
+            // that an access touches 8 columns (a thread per column touched 64: 31000 clocks
+            // per panel at 118 unknowns, 16000 like this)
+            const int r8 = t % 8, c16 = t / kWave * 16 + t % kWave / 8;
+            double v[8], d[8];
+            int to[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int i = 8 * g + r8;
+                const int from = i < nb ? S.e.src[i] : 0;
+                to[g] = moved && i < nb ? S.e.dst[i] : -1;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const double* Ac = A + (long long)(c0 + min(c16 + 8 * h, w - 1)) * m + k0;
+                    v[2 * g + h] = Ac[from];
+                    d[2 * g + h] = Ac[i < nb ? i : 0];
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int c = c16 + 8 * h;
+                    S.e.u[8 * g + r8][c] = 8 * g + r8 < nb && c < w ? v[2 * g + h] : 0.0;
+                    // every row of this column is read, by this wave, before any is written
+                    if (to[g] >= 0 && c < w) A[(long long)(c0 + c) * m + k0 + to[g]] = d[2 * g + h];
+                }
+            __syncthreads();
+            if (t < w) {
                 double u[NB];
 #pragma unroll
-                for (int i = 0; i < NB; ++i) u[i] = 0.0;
-                if (t < w)
-                    move_and_solve<NB>(A + (long long)(c0 + t) * m + k0, nb, moved, S.e.src, S.e.dst, &S.e.l[0][0],
-                                       kOneRows, 1.0, true, u);
+                for (int i = 0; i < NB; ++i) u[i] = S.e.u[i][t];
+                solve_lower<NB>(&S.e.l[0][0], kOneRows, 1.0, u);
 #pragma unroll
                 for (int i = 0; i < NB; ++i) S.e.u[i][t] = u[i];
             }
             __syncthreads();
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int c = c16 + 8 * h;
+                    if (8 * g + r8 < nb && c < w) A[(long long)(c0 + c) * m + k0 + 8 * g + r8] = S.e.u[8 * g + r8][c];
+                }
             const int tr = (mr - nb + 31) / 32, tc = (w + 31) / 32;
             for (int e = wave; e < tr * tc; e += kSolveWaves) {
                 const int ir = e % tr, ic = e / tr;
@@ -743,7 +807,12 @@ constexpr int kSwapThreads = 256;
 static_assert(kWave % kOuterNB == 0, "a column's touched rows are read by one wave");
 constexpr int kUpdTile = 64;               // the update kernel's tile: 4 waves of 32 x 32
 constexpr int kUpdThreads = 256;
+constexpr int kWaitRows = 128;             // rows of a tile of the waiting update
 constexpr int kUpdStride = kUpdTile + 16;  // LDS stride of its operands (16 mod 32: no conflicts)
+// Work-groups go to the XCDs in turn, so every eighth one of a launch lands beside
+// work-group 0, the panel's.  With the panel's columns written from there the panel
+// kernel loads 4000 x 8 entries in 10000 clocks; from all XCDs 25000.
+constexpr int kXcds = 8;
 constexpr int kAboveRows = 64;             // rows per work-group of solve_back_above_kernel
 static_assert(kOuterNB <= kWave, "the swap kernel's mapping keeps two touched rows per lane of one wave");
 static_assert(kMultiMin > kSingularSlot, "x must hold the pivots and the flag");
@@ -756,7 +825,41 @@ struct OuterArgs {
     int m, k0, nbo;              // outer panel: columns k0 .. k0 + nbo - 1
     int kk, nb;                  // panel and update kernels: columns kk .. kk + nb - 1 of it
     long long c0, c1;            // update kernel: columns c0 .. c1 - 1
+    int spread;                  // update kernel: one of `spread` work-groups has a tile
+    int w0, row_tiles;           // panel kernel: its first tile of the waiting update, and that update's row tiles
+    long long wc0;               // first column of the waiting update (panel k0 - kOuterNB, columns wc0 .. ld - 1)
 };
+
+// A22 -= L21 U12 for one tile of ROWS x kUpdTile entries from (rb, cb) on (columns below
+// c1), L21 and U12 from panel columns kk .. kk + nb - 1, one 32 x 32 part per wave at a time.
+template <int ROWS>
+struct UpdateLds {
+    double l[kOuterNB * (ROWS + 16)];        // -L21: [k][row]
+    double u[kOuterNB * kUpdStride];         // U12: [k][column]
+};
+template <int ROWS>
+__device__ __forceinline__ void update_tile(double* A, long long m, int kk, int nb, long long rb, long long cb,
+                                            long long c1, int threads, UpdateLds<ROWS>& S) {
+    constexpr int ls = ROWS + 16;
+    const int t = threadIdx.x, nd = (nb + 3) / 4 * 4;
+    for (int e = t; e < ROWS * nd; e += threads) {
+        const int k = e / ROWS, r = e % ROWS;
+        S.l[k * ls + r] = (k < nb && rb + r < m) ? -A[(kk + k) * m + rb + r] : 0.0;
+    }
+    for (int e = t; e < kUpdTile * nd; e += threads) {
+        const int cc = e / nd, k = e - cc * nd;
+        S.u[k * kUpdStride + cc] = (k < nb && cb + cc < c1) ? A[(cb + cc) * m + kk + k] : 0.0;
+    }
+    __syncthreads();
+    for (int part = t / kWave; part < ROWS / 16; part += threads / kWave) {
+        const int wr = 32 * (part % (ROWS / 32)), wc = 32 * (part / (ROWS / 32));
+        if (rb + wr >= m || cb + wc >= c1) continue;
+        UpdateTile<false> T;
+        T.load(A, m, rb + wr, cb + wc, m, c1);
+        T.multiply(S.l + wr, ls, S.u + wc, kUpdStride, nd);
+        T.store(A, m, rb + wr, cb + wc, m, c1);
+    }
+}
 
 // 32 x 32 tiles of [K | C~] through LDS, from rows of K to columns of the workspace.
 constexpr int kAsmTile = 32;
@@ -778,26 +881,45 @@ __global__ void __launch_bounds__(256) solve_assemble_kernel(SolveArgs a) {
 // One work-group factorises columns kk .. kk + nb - 1 (rows kk .. m - 1) of the
 // outer panel in registers and applies the exchanges to the outer panel's
 // other columns, with U12 for those on the right.  Bound by one compute unit's
-// reach: the column chains (2000 .. 3000 clocks each) and, for tall panels, its
-// loads and stores (10 .. 15 bytes per clock).  Per 32 columns at about 3000
-// rows: 4 launches of 25 us (one of 220 us before, which streamed the outer
-// panel through L2 for every inner panel's update).
+// reach: of 60000 .. 65000 clocks for 8 columns of 3000 .. 4000 rows the column
+// chains take 30000, the loads 10000 (see kXcds) and the stores 6000.  The other
+// work-groups do the waiting update of the columns beyond (none of its launches is
+// longer for it below 5000 unknowns): 4000 unknowns 18.5 -> 17.0 ms, 9000 100 -> 84
+// ms; with the columns written from one XCD and one barrier per column 15.5 and 82.
 template <int NB, int RPT, int T = kSolveThreads>
 __global__ void __launch_bounds__(T) solve_panel_kernel(OuterArgs a) {
-    __shared__ PivotLds<NB> P;
-    __shared__ double s_l[NB][NB];           // L11 by columns
-    __shared__ int s_src[NB], s_dst[NB], s_moved;
+    struct Panel {
+        PivotLds<NB> p;
+        double l[NB][NB];                    // L11 by columns
+        int src[NB], dst[NB], moved;
+    };
+    __shared__ union Lds {
+        Panel f;
+        UpdateLds<kWaitRows> u;
+    } S;
     const int t = threadIdx.x;
     const int m = a.m, kk = a.kk, nb = a.nb, mr = m - kk;
     double* A = a.A;
     if (a.x[kSingularSlot] != 0.0) return;   // an earlier panel was singular
+    if constexpr (T <= kSolveThreads) {
+        if (blockIdx.x > 0) {
+            const int w = a.w0 + (int)blockIdx.x - 1;
+            update_tile(A, m, a.k0 - kOuterNB, kOuterNB, a.k0 + (long long)(w % a.row_tiles) * kWaitRows,
+                        a.wc0 + (long long)(w / a.row_tiles) * kUpdTile, a.ld, blockDim.x, S.u);
+            return;
+        }
+    }
+    PivotLds<NB>& P = S.f.p;
+    double (&s_l)[NB][NB] = S.f.l;
+    int (&s_src)[NB] = S.f.src;
+    int (&s_dst)[NB] = S.f.dst;
+    int& s_moved = S.f.moved;
     if (t == 0) P.sing = s_moved = 0;
     __syncthreads();
     const int waves = min((int)blockDim.x, mr + kWave - 1) / kWave;
     PanelRows<NB, RPT> R;
     load_rows<NB, RPT>(R, A, m, kk, mr, nb, waves);
     factor_rows<NB, RPT>(R, nb, waves, P);
-    if (waves == 1) __syncthreads();         // blk and piv for every wave (the last column's barrier otherwise)
     if (P.sing) {                            // positions hold nothing of use then
         if (t == 0) a.x[kSingularSlot] = 1.0;
         return;
@@ -916,13 +1038,7 @@ __global__ void __launch_bounds__(kSwapThreads) solve_swap_trsm_kernel(OuterArgs
         double u[kOuterNB];
 #pragma unroll
         for (int r = 0; r < kOuterNB; ++r) u[r] = s_tile[t][r];
-        int ofs = 0;
-#pragma unroll
-        for (int r = 0; r < kOuterNB; ++r) {
-            asm volatile("" : "+v"(ofs), "+v"(u[r]));   // a column of L11 is read when its turn comes, not before
-#pragma unroll
-            for (int j = r + 1; j < kOuterNB; ++j) u[j] = __builtin_fma(-s_l[r][ofs + j], u[r], u[j]);
-        }
+        solve_lower<kOuterNB>(&s_l[0][0], kOuterNB, -1.0, u);
 #pragma unroll
         for (int r = 0; r < kOuterNB; ++r) s_tile[t][r] = u[r];
     }
@@ -940,30 +1056,13 @@ __global__ void __launch_bounds__(kSwapThreads) solve_swap_trsm_kernel(OuterArgs
 // 65 us for the first one at 4000 unknowns (94 us before, on the vector unit,
 // one work-group's loads after another).
 __global__ void __launch_bounds__(kUpdThreads) solve_update_kernel(OuterArgs a) {
-    __shared__ double s_l[kOuterNB * kUpdStride];      // -L21: [k][row]
-    __shared__ double s_u[kOuterNB * kUpdStride];      // U12: [k][column]
+    __shared__ UpdateLds<kUpdTile> S;
     if (a.x[kSingularSlot] != 0.0) return;
-    const int t = threadIdx.x;
-    const long long m = a.m;
-    const int kk = a.kk, nb = a.nb, nd = (nb + 3) / 4 * 4;
-    const long long rb = (long long)kk + nb + (long long)blockIdx.x * kUpdTile;
+    // the next panel's columns: all tiles on the panel kernel's XCD, whose L2 then holds them
+    if (blockIdx.x % a.spread) return;
+    const long long rb = (long long)a.kk + a.nb + (long long)(blockIdx.x / a.spread) * kUpdTile;
     const long long cb = a.c0 + (long long)blockIdx.y * kUpdTile;
-    double* A = a.A;
-    for (int e = t; e < kUpdTile * nd; e += kUpdThreads) {
-        const int k = e / kUpdTile, r = e % kUpdTile;
-        s_l[k * kUpdStride + r] = (k < nb && rb + r < m) ? -A[(kk + k) * m + rb + r] : 0.0;
-    }
-    for (int e = t; e < kUpdTile * nd; e += kUpdThreads) {
-        const int cc = e / nd, k = e - cc * nd;
-        s_u[k * kUpdStride + cc] = (k < nb && cb + cc < a.c1) ? A[(cb + cc) * m + kk + k] : 0.0;
-    }
-    __syncthreads();
-    const int wave = t / kWave, wr = 32 * (wave % 2), wc = 32 * (wave / 2);
-    if (rb + wr >= m || cb + wc >= a.c1) return;
-    UpdateTile<false> T;
-    T.load(A, m, rb + wr, cb + wc, m, a.c1);
-    T.multiply(s_l + wr, kUpdStride, s_u + wc, kUpdStride, nd);
-    T.store(A, m, rb + wr, cb + wc, m, a.c1);
+    update_tile(a.A, a.m, a.kk, a.nb, rb, cb, a.c1, kUpdThreads, S);
 }
 
 struct BackArgs {
@@ -1077,47 +1176,59 @@ hipError_t launch_master_solve(int pol, int n, const double* K, int n_rhs, const
     o.x = x;
     o.ld = ld;
     o.m = m;
+    // columns of the widest panel whose rows fit in registers (64 doubles per thread)
+    auto panel_width = [](int rows) {
+        return rows <= 2 * kSolveThreads ? 32 : rows <= 4 * kSolveThreads ? 16 : rows <= 8 * kSolveThreads ? 8
+               : rows <= 16 * kSolveThreads ? 4 : 2;
+    };
     auto update = [&](long long c0, long long c1) {
         const long long rows = m - (o.kk + o.nb);
         if (rows <= 0 || c1 <= c0) return;
         o.c0 = c0;
+        o.spread = c1 - c0 <= kOuterNB ? kXcds : 1;
         o.c1 = c1;
         hipLaunchKernelGGL(solve_update_kernel,
-                           dim3((unsigned)((rows + kUpdTile - 1) / kUpdTile), (unsigned)((c1 - c0 + kUpdTile - 1) / kUpdTile)),
+                           dim3((unsigned)((rows + kUpdTile - 1) / kUpdTile * o.spread), (unsigned)((c1 - c0 + kUpdTile - 1) / kUpdTile)),
                            dim3(kUpdThreads), 0, s, o);
     };
     for (int k0 = 0; k0 < m; k0 += kOuterNB) {
         o.k0 = k0;
         o.nbo = std::min(kOuterNB, m - k0);
         const int ce = k0 + o.nbo;
-        // the widest panel whose rows fit in registers (64 doubles per thread), chosen by
-        // the outer panel's first column
-        const int mr0 = m - k0;
-        const int nb = mr0 <= 2 * kSolveThreads ? 32 : mr0 <= 4 * kSolveThreads ? 16 : mr0 <= 8 * kSolveThreads ? 8
-                       : mr0 <= 16 * kSolveThreads ? 4 : 2;
-        for (int kk = k0; kk < ce; kk += nb) {
+        // chosen by the outer panel's first column
+        const int nb = panel_width(m - k0);
+        // the update that the previous outer panel left waiting, spread over this one's launches
+        o.wc0 = ce;
+        o.row_tiles = (m - k0 + kWaitRows - 1) / kWaitRows;
+        const long long waiting = k0 && nb > 2 ? o.row_tiles * ((ld - ce + kUpdTile - 1) / kUpdTile) : 0;
+        const int launches = (o.nbo + nb - 1) / nb;
+        for (int kk = k0, i = 0; kk < ce; kk += nb, ++i) {
             o.kk = kk;
             o.nb = std::min(nb, ce - kk);
+            o.w0 = (int)(waiting * i / launches);
+            const dim3 grid(1 + (unsigned)(waiting * (i + 1) / launches - o.w0));
             const int mr = m - kk;
             if (nb == 32 && mr <= kSolveThreads)
-                hipLaunchKernelGGL((solve_panel_kernel<32, 1>), dim3(1), dim3((unsigned)((mr + kWave - 1) / kWave * kWave)), 0, s, o);
+                hipLaunchKernelGGL((solve_panel_kernel<32, 1>), grid, dim3((unsigned)((mr + kWave - 1) / kWave * kWave)), 0, s, o);
             else if (nb == 32)
-                hipLaunchKernelGGL((solve_panel_kernel<32, 2>), dim3(1), dim3(kSolveThreads), 0, s, o);
+                hipLaunchKernelGGL((solve_panel_kernel<32, 2>), grid, dim3(kSolveThreads), 0, s, o);
             else if (nb == 16)
-                hipLaunchKernelGGL((solve_panel_kernel<16, 4>), dim3(1), dim3(kSolveThreads), 0, s, o);
+                hipLaunchKernelGGL((solve_panel_kernel<16, 4>), grid, dim3(kSolveThreads), 0, s, o);
             else if (nb == 8)
-                hipLaunchKernelGGL((solve_panel_kernel<8, 8>), dim3(1), dim3(kSolveThreads), 0, s, o);
+                hipLaunchKernelGGL((solve_panel_kernel<8, 8>), grid, dim3(kSolveThreads), 0, s, o);
             else if (nb == 4)
-                hipLaunchKernelGGL((solve_panel_kernel<4, 16>), dim3(1), dim3(kSolveThreads), 0, s, o);
+                hipLaunchKernelGGL((solve_panel_kernel<4, 16>), grid, dim3(kSolveThreads), 0, s, o);
             else
-                hipLaunchKernelGGL((solve_panel_kernel<2, 16, kTallThreads>), dim3(1), dim3(kTallThreads), 0, s, o);
+                hipLaunchKernelGGL((solve_panel_kernel<2, 16, kTallThreads>), grid, dim3(kTallThreads), 0, s, o);
             update(kk + o.nb, ce);               // the outer panel's later columns
         }
         o.kk = k0;
         o.nb = o.nbo;
         const unsigned col_groups = (unsigned)((ld - ce + kSwapCols - 1) / kSwapCols);   // >= 1: right-hand sides
         hipLaunchKernelGGL(solve_swap_trsm_kernel, dim3(col_groups), dim3(kSwapThreads), 0, s, o);
-        update(ce, ld);
+        // the next outer panel's columns now, the others beside its factorisation (not in the
+        // panel kernel for two columns: its 1024 threads leave too few registers)
+        update(ce, ce < m && panel_width(m - ce) > 2 ? std::min(ce + kOuterNB, m) : ld);
     }
     BackArgs b;
     b.A = work;

@@ -1,0 +1,28 @@
+"""The MASTER solve's update that waits beside the next panel: rows beyond the widest
+panels (above 8192, where the two-column panels take no such update, then below), and
+right-hand sides enough that they fill tiles of their own; and the one-work-group
+path's exchanges over one and several groups of 128 columns.
+
+Dense Gaussian matrices exchange rows in nearly every column.  The bound is the backward
+error of Gaussian elimination with partial pivoting, 64 m eps.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n_rhs", [(97, 32), (200, 129), (383, 140), (416, 1), (447, 65), (700, 200), (8230, 2)])
+def test_waiting_update(m, n_rhs):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_15605_amd import couple
+    g = torch.Generator().manual_seed(m)
+    A = torch.randn(m, m, generator=g, dtype=torch.float64).cuda()
+    b = torch.randn(n_rhs, m, generator=g, dtype=torch.float64).cuda()
+    ctx = couple.couple_init(8)
+    x = couple.couple_master_solve(ctx, A, b)
+    res = (A @ x.T - b.T).abs().max().item()
+    scale = (A.abs().sum(1).max() * x.abs().max() + b.abs().max()).item()
+    assert res <= 64 * m * np.finfo(float).eps * scale, (m, res / scale)
