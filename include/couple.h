@@ -352,8 +352,8 @@ int couple_threej_rows_m(couple_ctx *ctx, int m1, int m2, int n_pairs, const int
  *   work : device float64 workspace of m * (m + n_rhs) entries, overwritten.
  *   x    : device float64 [n_rhs][m], the solution.
  *   m + n_rhs <= 15840.  Gaussian elimination with partial pivoting in
- *   float64; K and rhs are not modified.  Below 384 unknowns one work-group
- *   runs it all (one kernel).  From 384 on, outer panels of 32 columns are
+ *   float64; K and rhs are not modified.  Below 192 unknowns one work-group
+ *   runs it all (one kernel).  From 192 on, outer panels of 32 columns are
  *   factorised by one work-group each while the row exchanges, U12 and the
  *   trailing updates are spread over the chip; x serves as the scratch for
  *   each panel's pivots until the back substitution

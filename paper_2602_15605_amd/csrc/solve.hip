@@ -653,7 +653,9 @@ __device__ inline void back_block(double* A, long long m, int lo, int hi, int r0
 }
 
 constexpr int kOuterNB = 32;               // columns per outer panel
-constexpr int kMultiMin = 384;             // systems of at least this many unknowns take the multi-work-group path
+// Systems of at least this many unknowns take the multi-work-group path (one work-group /
+// several, us): 176 296 / 301, 192 330 / 317, 256 496 / 437, 320 724 / 577, 383 995 / 712.
+constexpr int kMultiMin = 192;
 constexpr int kOneRows = kMultiMin + 48;   // LDS row stride of L21 in the one-work-group path: the rows and a tile's
                                            // remainder, 16 mod 32 (no conflicts)
 constexpr int kOneCols = 128;              // columns of U12 staged at a time there
@@ -815,6 +817,10 @@ constexpr int kUpdStride = kUpdTile + 16;  // LDS stride of its operands (16 mod
 constexpr int kXcds = 8;
 constexpr int kAboveRows = 64;             // rows per work-group of solve_back_above_kernel
 static_assert(kOuterNB <= kWave, "the swap kernel's mapping keeps two touched rows per lane of one wave");
+// Systems of fewer unknowns add the products of an update one by one (UpdateTile), as the
+// one-work-group path does, so that equal rows cancel exactly and give NaN.
+constexpr int kChainBelow = 384;
+static_assert(kChainBelow <= kSolveThreads, "their panels are 32 columns with one row per thread");
 static_assert(kMultiMin > kSingularSlot, "x must hold the pivots and the flag");
 static_assert(kMultiMin <= kBackRows && kMultiMin <= kSolveThreads, "one row per thread and one back block below it");
 
@@ -837,7 +843,7 @@ struct UpdateLds {
     double l[kOuterNB * (ROWS + 16)];        // -L21: [k][row]
     double u[kOuterNB * kUpdStride];         // U12: [k][column]
 };
-template <int ROWS>
+template <bool CHAIN, int ROWS>
 __device__ __forceinline__ void update_tile(double* A, long long m, int kk, int nb, long long rb, long long cb,
                                             long long c1, int threads, UpdateLds<ROWS>& S) {
     constexpr int ls = ROWS + 16;
@@ -854,7 +860,7 @@ __device__ __forceinline__ void update_tile(double* A, long long m, int kk, int 
     for (int part = t / kWave; part < ROWS / 16; part += threads / kWave) {
         const int wr = 32 * (part % (ROWS / 32)), wc = 32 * (part / (ROWS / 32));
         if (rb + wr >= m || cb + wc >= c1) continue;
-        UpdateTile<false> T;
+        UpdateTile<CHAIN> T;
         T.load(A, m, rb + wr, cb + wc, m, c1);
         T.multiply(S.l + wr, ls, S.u + wc, kUpdStride, nd);
         T.store(A, m, rb + wr, cb + wc, m, c1);
@@ -868,7 +874,6 @@ __global__ void __launch_bounds__(256) solve_assemble_kernel(SolveArgs a) {
     const int r0 = blockIdx.y * kAsmTile, c0 = blockIdx.x * kAsmTile;
     const int lo = threadIdx.x % kAsmTile, up = threadIdx.x / kAsmTile;
     const int ld = a.m + a.n_rhs;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.x[kSingularSlot] = 0.0;
 #pragma unroll
     for (int q = 0; q < kAsmTile; q += 8)
         if (r0 + up + q < a.m && c0 + lo < ld) v[up + q][lo] = assembled(a, r0 + up + q, c0 + lo);
@@ -886,7 +891,7 @@ __global__ void __launch_bounds__(256) solve_assemble_kernel(SolveArgs a) {
 // work-groups do the waiting update of the columns beyond (none of its launches is
 // longer for it below 5000 unknowns): 4000 unknowns 18.5 -> 17.0 ms, 9000 100 -> 84
 // ms; with the columns written from one XCD and one barrier per column 15.5 and 82.
-template <int NB, int RPT, int T = kSolveThreads>
+template <int NB, int RPT, bool CHAIN = false, int T = kSolveThreads>
 __global__ void __launch_bounds__(T) solve_panel_kernel(OuterArgs a) {
     struct Panel {
         PivotLds<NB> p;
@@ -900,11 +905,16 @@ __global__ void __launch_bounds__(T) solve_panel_kernel(OuterArgs a) {
     const int t = threadIdx.x;
     const int m = a.m, kk = a.kk, nb = a.nb, mr = m - kk;
     double* A = a.A;
-    if (a.x[kSingularSlot] != 0.0) return;   // an earlier panel was singular
+    // the first panel clears the flag (not the assembly: x may be the right-hand side)
+    if (kk == 0) {
+        if (t == 0) a.x[kSingularSlot] = 0.0;
+    } else if (a.x[kSingularSlot] != 0.0) {
+        return;                              // an earlier panel was singular
+    }
     if constexpr (T <= kSolveThreads) {
         if (blockIdx.x > 0) {
             const int w = a.w0 + (int)blockIdx.x - 1;
-            update_tile(A, m, a.k0 - kOuterNB, kOuterNB, a.k0 + (long long)(w % a.row_tiles) * kWaitRows,
+            update_tile<CHAIN>(A, m, a.k0 - kOuterNB, kOuterNB, a.k0 + (long long)(w % a.row_tiles) * kWaitRows,
                         a.wc0 + (long long)(w / a.row_tiles) * kUpdTile, a.ld, blockDim.x, S.u);
             return;
         }
@@ -1055,6 +1065,7 @@ __global__ void __launch_bounds__(kSwapThreads) solve_swap_trsm_kernel(OuterArgs
 // Bound by the trailing matrix's traffic, 16 bytes per entry and outer panel:
 // 65 us for the first one at 4000 unknowns (94 us before, on the vector unit,
 // one work-group's loads after another).
+template <bool CHAIN>
 __global__ void __launch_bounds__(kUpdThreads) solve_update_kernel(OuterArgs a) {
     __shared__ UpdateLds<kUpdTile> S;
     if (a.x[kSingularSlot] != 0.0) return;
@@ -1062,7 +1073,7 @@ __global__ void __launch_bounds__(kUpdThreads) solve_update_kernel(OuterArgs a) 
     if (blockIdx.x % a.spread) return;
     const long long rb = (long long)a.kk + a.nb + (long long)(blockIdx.x / a.spread) * kUpdTile;
     const long long cb = a.c0 + (long long)blockIdx.y * kUpdTile;
-    update_tile(a.A, a.m, a.kk, a.nb, rb, cb, a.c1, kUpdThreads, S);
+    update_tile<CHAIN>(a.A, a.m, a.kk, a.nb, rb, cb, a.c1, kUpdThreads, S);
 }
 
 struct BackArgs {
@@ -1181,15 +1192,18 @@ hipError_t launch_master_solve(int pol, int n, const double* K, int n_rhs, const
         return rows <= 2 * kSolveThreads ? 32 : rows <= 4 * kSolveThreads ? 16 : rows <= 8 * kSolveThreads ? 8
                : rows <= 16 * kSolveThreads ? 4 : 2;
     };
+    const bool chain = m < kChainBelow;
     auto update = [&](long long c0, long long c1) {
         const long long rows = m - (o.kk + o.nb);
         if (rows <= 0 || c1 <= c0) return;
         o.c0 = c0;
         o.spread = c1 - c0 <= kOuterNB ? kXcds : 1;
         o.c1 = c1;
-        hipLaunchKernelGGL(solve_update_kernel,
-                           dim3((unsigned)((rows + kUpdTile - 1) / kUpdTile * o.spread), (unsigned)((c1 - c0 + kUpdTile - 1) / kUpdTile)),
-                           dim3(kUpdThreads), 0, s, o);
+        const dim3 grid((unsigned)((rows + kUpdTile - 1) / kUpdTile * o.spread), (unsigned)((c1 - c0 + kUpdTile - 1) / kUpdTile));
+        if (chain)
+            hipLaunchKernelGGL(solve_update_kernel<true>, grid, dim3(kUpdThreads), 0, s, o);
+        else
+            hipLaunchKernelGGL(solve_update_kernel<false>, grid, dim3(kUpdThreads), 0, s, o);
     };
     for (int k0 = 0; k0 < m; k0 += kOuterNB) {
         o.k0 = k0;
@@ -1208,7 +1222,9 @@ hipError_t launch_master_solve(int pol, int n, const double* K, int n_rhs, const
             o.w0 = (int)(waiting * i / launches);
             const dim3 grid(1 + (unsigned)(waiting * (i + 1) / launches - o.w0));
             const int mr = m - kk;
-            if (nb == 32 && mr <= kSolveThreads)
+            if (chain)
+                hipLaunchKernelGGL((solve_panel_kernel<32, 1, true>), grid, dim3((unsigned)((mr + kWave - 1) / kWave * kWave)), 0, s, o);
+            else if (nb == 32 && mr <= kSolveThreads)
                 hipLaunchKernelGGL((solve_panel_kernel<32, 1>), grid, dim3((unsigned)((mr + kWave - 1) / kWave * kWave)), 0, s, o);
             else if (nb == 32)
                 hipLaunchKernelGGL((solve_panel_kernel<32, 2>), grid, dim3(kSolveThreads), 0, s, o);
@@ -1219,7 +1235,7 @@ hipError_t launch_master_solve(int pol, int n, const double* K, int n_rhs, const
             else if (nb == 4)
                 hipLaunchKernelGGL((solve_panel_kernel<4, 16>), grid, dim3(kSolveThreads), 0, s, o);
             else
-                hipLaunchKernelGGL((solve_panel_kernel<2, 16, kTallThreads>), grid, dim3(kTallThreads), 0, s, o);
+                hipLaunchKernelGGL((solve_panel_kernel<2, 16, false, kTallThreads>), grid, dim3(kTallThreads), 0, s, o);
             update(kk + o.nb, ce);               // the outer panel's later columns
         }
         o.kk = k0;

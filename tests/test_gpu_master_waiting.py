@@ -3,6 +3,9 @@ panels (above 8192, where the two-column panels take no such update, then below)
 right-hand sides enough that they fill tiles of their own; and the one-work-group
 path's exchanges over one and several groups of 128 columns.
 
+Equal rows below 384 unknowns, on either side of the 192 at which several work-groups
+take over: they cancel exactly, so the matrix is singular and everything NaN.
+
 Dense Gaussian matrices exchange rows in nearly every column.  The bound is the backward
 error of Gaussian elimination with partial pivoting, 64 m eps.
 """
@@ -12,7 +15,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,n_rhs", [(97, 32), (200, 129), (383, 140), (416, 1), (447, 65), (700, 200), (8230, 2)])
+@pytest.mark.parametrize("m,n_rhs", [(97, 32), (191, 129), (192, 129), (223, 1), (383, 140), (416, 1), (447, 65), (700, 200), (8230, 2)])
 def test_waiting_update(m, n_rhs):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
@@ -26,3 +29,32 @@ def test_waiting_update(m, n_rhs):
     res = (A @ x.T - b.T).abs().max().item()
     scale = (A.abs().sum(1).max() * x.abs().max() + b.abs().max()).item()
     assert res <= 64 * m * np.finfo(float).eps * scale, (m, res / scale)
+
+
+@pytest.mark.parametrize("m,i,j", [(191, 5, 190), (192, 5, 190), (192, 0, 1), (300, 40, 170), (383, 3, 382)])
+def test_equal_rows_give_nan(m, i, j):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_15605_amd import couple
+    g = torch.Generator().manual_seed(m + j)
+    A = torch.randn(m, m, generator=g, dtype=torch.float64)
+    A[j] = A[i]
+    ctx = couple.couple_init(8)
+    x = couple.couple_master_solve(ctx, A.cuda(), torch.ones(m, dtype=torch.float64).cuda())
+    assert torch.isnan(x).all()
+
+
+@pytest.mark.parametrize("m", [100, 192, 300, 1100])
+def test_solution_over_the_right_hand_side(m):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2602_15605_amd import couple
+    g = torch.Generator().manual_seed(m)
+    A = torch.randn(m, m, generator=g, dtype=torch.float64).cuda()
+    b = torch.randn(2, m, generator=g, dtype=torch.float64).cuda()
+    ctx = couple.couple_init(8)
+    want = couple.couple_master_solve(ctx, A, b)
+    couple.couple_master_solve(ctx, A, b, out=b)
+    assert torch.equal(b, want)
