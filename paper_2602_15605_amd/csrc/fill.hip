@@ -2,7 +2,7 @@
 //
 // Xi is symmetric in (l1, l2); K is not: K_{l1 l2} = (2 l2 + 1) Xi(l1, l2)
 // (Sec. 2 eqs. K_TT, K_EE; App. A).  The paper fills the lower triangle from
-// the upper one (Sec. 4.1); here that is done on Xi, and each 64 x 64 tile
+// the upper one (Sec. 4.1); here that is done on Xi, and each tile
 // of K is written with its own column factor.
 //
 // fill: one work-group per upper tile pair (I <= J) of one job (a Xi store
@@ -10,8 +10,7 @@
 // diagonal by diagonal (consecutive l1 are consecutive in memory), kept in
 // LDS, and written twice: K[l1][l2] row by row and the mirrored tile
 // K[l2][l1] = (2 l1 + 1) Xi(l1, l2), also row by row, so both halves are
-// coalesced.  K is written once and never read back here, so the stores
-// are non-temporal.  K^BB is written from the same LDS values as K^EE.  Xi_EB is
+// coalesced.  K^BB is written from the same LDS values as K^EE.  Xi_EB is
 // symmetric as well (the (-2 2 0)^2 of odd L is even under l1 <-> l2).
 //
 // bin: K_{b b'} = (1/n_b) sum_{l1 in b} sum_{l2 in b'} K_{l1 l2}; one
@@ -22,7 +21,17 @@
 namespace couple {
 namespace {
 
-constexpr int kT = 64;           // tile edge
+constexpr int kFillWays = 8;     // threads per tile column: a thread's T / kFillWays loads are in flight together
+// The tile edge by the matrix entries that a launch writes: 16 and 32 spread small
+// matrices over more work-groups.  Per call (float32 sums, this kernel with 16 / 32 / 64):
+// TT + TE + EE + BB at lmax 256 28.7 / 29.8 / 33.7 us (the 64 x 64 tiles before, loaded
+// one diagonal after another, 52.7), 500 44.0 / 44.0 / 47.5 (66.3), 1000 89 / 87 / 87
+// (104), 2000 331 / 321 / 317 (338); TT at lmax 3000 323 / 317 / 312 (324).
+constexpr long long kFill32Entries = 600000, kFill64Entries = 6000000;
+// fill_large_kernel from here on (400 MB, above what the memory-side cache holds): plain
+// stores / past the caches at lmax 4500, four matrices, 2916 / 2830 us; lmax 3000 922 / 933.
+constexpr long long kFillPastEntries = 50000000;
+constexpr int kT = 64;           // the largest tile edge
 constexpr int kFillThreads = 512;  // 8 waves per tile: more stores in flight per LDS tile
 
 struct FillArgs {
@@ -33,8 +42,78 @@ struct FillArgs {
     int src[kMaxOut];            // Xi index of each output
 };
 
-__device__ inline void pair_from_index(int t, int n, int* I, int* J) {
-    // t enumerates (I, J), I <= J, row by row: row I holds n - I pairs
+// t enumerates (I, J), I <= J < n, column by column: column J holds J + 1 pairs.
+__device__ inline void pair_from_index(int t, int* I, int* J) {
+    int j = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while ((j + 1) * (j + 2) / 2 <= t) ++j;
+    while (j * (j + 1) / 2 > t) --j;
+    *J = j;
+    *I = t - j * (j + 1) / 2;
+}
+
+// T x T tiles by kFillWays T threads.  What bounds it: memory (at lmax 3000, four matrices,
+// 0.4 GB in 100 us, the large form 120 us), and for small matrices the chain of a load,
+// an exchange through LDS and a store.
+template <int T>
+__global__ void __launch_bounds__(kFillWays * T) fill_kernel(FillArgs a) {
+    constexpr int kPer = T / kFillWays;
+    __shared__ double tile[T][T + 1];
+    // job of this block: blocks [block0, block0 + n_tiles (n_tiles + 1) / 2) of each job
+    int jb = 0;
+    while (jb + 1 < a.n_jobs && (int)blockIdx.x >= a.job[jb + 1].block0) ++jb;
+    const FillJob& job = a.job[jb];
+    const int lmax = job.lmax;
+    int I, J;
+    pair_from_index((int)blockIdx.x - job.block0, &I, &J);
+    const int r0 = T * I, c0 = T * J;
+    const int lo = threadIdx.x % T, up = threadIdx.x / T;
+    const long long ld = lmax + 1;
+    int last_src = -1;
+    for (int o = 0; o < a.n_out; ++o) {
+        const int src = a.src[o];
+        if (src != last_src) {
+            const double* xi = job.xi + (long long)src * job.xi_stride;
+            // element (r, (r + w) mod T): for one w the lanes run along two diagonals
+            double v[kPer];
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const int l1 = r0 + lo, l2 = c0 + ((lo + up + kFillWays * q) & (T - 1)), d = l2 - l1;
+                const bool in = l2 <= lmax && d >= 0 && d <= job.dmax;
+                v[q] = in ? xi[diag_offset(lmax, d) + l1] : 0.0;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) tile[lo][(lo + up + kFillWays * q) & (T - 1)] = v[q];
+            __syncthreads();
+            last_src = src;
+        }
+        double* out = job.out + (long long)o * ld * ld;
+        // column factor fs l + 1: 2 l + 1 for K, 1 for Xi
+        const double fs = a.xi_only ? 0.0 : 2.0;
+        const int l2 = c0 + lo;
+        if (l2 <= lmax) {
+            const double f = fs * l2 + 1.0;
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const int r = up + kFillWays * q, l1 = r0 + r;
+                const double x = I == J && lo < r ? tile[lo][r] : tile[r][lo];
+                if (l1 <= lmax) out[l1 * ld + l2] = f * x;
+            }
+        }
+        if (I != J) {
+            const int l1 = r0 + lo;
+            const double f = fs * l1 + 1.0;
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const int c = up + kFillWays * q;
+                if (c0 + c <= lmax) out[(c0 + c) * ld + l1] = f * tile[lo][c];
+            }
+        }
+    }
+}
+
+// t enumerates (I, J), I <= J < n, row by row: row I holds n - I pairs.
+__device__ inline void pair_by_rows(int t, int n, int* I, int* J) {
     int i = 0;
     int rem = t;
     while (rem >= n - i) {
@@ -45,8 +124,12 @@ __device__ inline void pair_from_index(int t, int n, int* I, int* J) {
     *J = i + rem;
 }
 
+// Launches of at least kFillPastEntries: 64 x 64 tiles, 512 threads, few registers, the
+// diagonals of a tile one after another, stores past the caches.  Bound by the memory's
+// writes (at lmax 6000, four matrices, 1.6 GB in 0.463 ms; fill_kernel<64> 0.476, the 32
+// masks of lmax 500 .. 4000 14.76 against 14.92 ms per call).
 __global__ void __launch_bounds__(kFillThreads)
-fill_kernel(FillArgs a) {
+fill_large_kernel(FillArgs a) {
     __shared__ double tile[kT][kT + 1];
     // job of this block: blocks [block0, block0 + n_tiles (n_tiles + 1) / 2) of each job
     int jb = 0;
@@ -54,7 +137,7 @@ fill_kernel(FillArgs a) {
     const FillJob& job = a.job[jb];
     const int lmax = job.lmax;
     int I, J;
-    pair_from_index((int)blockIdx.x - job.block0, (lmax + kT) / kT, &I, &J);
+    pair_by_rows((int)blockIdx.x - job.block0, (lmax + kT) / kT, &I, &J);
     const int r0 = kT * I, c0 = kT * J;
     const int t = threadIdx.x;
     const long long ld = lmax + 1;
@@ -260,18 +343,32 @@ hipError_t launch_fill_jobs(const FillJob* jobs, int n_jobs, const int* spec_src
                             hipStream_t s) {
     if (n_jobs < 1 || n_jobs > kMaxFillJobs) return hipErrorInvalidValue;
     FillArgs a;
-    long long blocks = 0;
-    for (int j = 0; j < n_jobs; ++j) {
-        a.job[j] = jobs[j];
-        a.job[j].block0 = (int)blocks;
-        const long long nt = (jobs[j].lmax + kT) / kT;
-        blocks += nt * (nt + 1) / 2;
-    }
     a.n_jobs = n_jobs;
     a.n_out = n_out;
     a.xi_only = xi;
     for (int i = 0; i < kMaxOut; ++i) a.src[i] = i < n_out ? spec_src[i] : 0;
-    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)blocks), dim3(kFillThreads), 0, s, a);
+    auto blocks = [&](int T) {
+        long long n = 0;
+        for (int j = 0; j < n_jobs; ++j) {
+            a.job[j] = jobs[j];
+            a.job[j].block0 = (int)n;
+            const long long nt = (jobs[j].lmax + T) / T;
+            n += nt * (nt + 1) / 2;
+        }
+        return dim3((unsigned)n);
+    };
+    long long entries = 0;
+    for (int j = 0; j < n_jobs; ++j) entries += (jobs[j].lmax + 1LL) * (jobs[j].lmax + 1LL) * n_out;
+    const int T = entries < kFill32Entries ? 16 : entries < kFill64Entries ? 32 : kT;
+    const dim3 grid = blocks(T);
+    if (entries >= kFillPastEntries)
+        hipLaunchKernelGGL(fill_large_kernel, grid, dim3(kFillThreads), 0, s, a);
+    else if (T == 16)
+        hipLaunchKernelGGL(fill_kernel<16>, grid, dim3(kFillWays * 16), 0, s, a);
+    else if (T == 32)
+        hipLaunchKernelGGL(fill_kernel<32>, grid, dim3(kFillWays * 32), 0, s, a);
+    else
+        hipLaunchKernelGGL(fill_kernel<kT>, grid, dim3(kFillWays * kT), 0, s, a);
     return hipGetLastError();
 }
 
