@@ -888,9 +888,10 @@ __global__ void __launch_bounds__(256) solve_assemble_kernel(SolveArgs a) {
 // other columns, with U12 for those on the right.  Bound by one compute unit's
 // reach: of 60000 .. 65000 clocks for 8 columns of 3000 .. 4000 rows the column
 // chains take 30000, the loads 10000 (see kXcds) and the stores 6000.  The other
-// work-groups do the waiting update of the columns beyond (none of its launches is
-// longer for it below 5000 unknowns): 4000 unknowns 18.5 -> 17.0 ms, 9000 100 -> 84
-// ms; with the columns written from one XCD and one barrier per column 15.5 and 82.
+// work-groups do the waiting update of the columns beyond, which took 65 us per outer
+// panel by itself at 4000 rows and adds 3 us to each of four launches here: 4000
+// unknowns 18.5 -> 17.0 ms, 9000 100 -> 84 ms; with the columns written from one XCD and
+// one barrier per column 15.5 and 82.
 template <int NB, int RPT, bool CHAIN = false, int T = kSolveThreads>
 __global__ void __launch_bounds__(T) solve_panel_kernel(OuterArgs a) {
     struct Panel {
@@ -1062,9 +1063,8 @@ __global__ void __launch_bounds__(kSwapThreads) solve_swap_trsm_kernel(OuterArgs
 
 // A22 -= L21 U12 over rows kk+nb .. m-1 and columns c0 .. c1-1, depth nb:
 // kUpdTile x kUpdTile entries per work-group, one 32 x 32 quarter per wave.
-// Bound by the trailing matrix's traffic, 16 bytes per entry and outer panel:
-// 65 us for the first one at 4000 unknowns (94 us before, on the vector unit,
-// one work-group's loads after another).
+// Only the columns that are needed next (the others wait, see solve_panel_kernel): bound
+// by its chain of loads, 5 .. 11 us per launch at 4000 unknowns.
 template <bool CHAIN>
 __global__ void __launch_bounds__(kUpdThreads) solve_update_kernel(OuterArgs a) {
     __shared__ UpdateLds<kUpdTile> S;
