@@ -356,9 +356,11 @@ int couple_threej_rows_m(couple_ctx *ctx, int m1, int m2, int n_pairs, const int
  *   runs it all (one kernel).  From 192 on, outer panels of 32 columns are
  *   factorised by one work-group each while the row exchanges, U12 and the
  *   trailing updates are spread over the chip; x serves as the scratch for
- *   each panel's pivots until the back substitution
- *   writes it.  A singular system (a zero pivot column) gives NaN in every
- *   entry of x.  Only enqueues kernels (no allocation, graph-capturable).
+ *   each panel's pivots until the back substitution writes it.  A singular
+ *   system (a zero pivot column) gives NaN in every entry of x.  Below 400
+ *   unknowns two equal rows cancel exactly and are found so; from 400 on they
+ *   leave rounding errors, and x holds finite values of no use.  Only enqueues
+ *   kernels (no allocation, graph-capturable).
  * Errors (both): EINVAL (NULL ctx or pointer, misaligned pointer, sizes or
  * edges out of range), EDEVICE.
  */

@@ -818,8 +818,10 @@ constexpr int kXcds = 8;
 constexpr int kAboveRows = 64;             // rows per work-group of solve_back_above_kernel
 static_assert(kOuterNB <= kWave, "the swap kernel's mapping keeps two touched rows per lane of one wave");
 // Systems of fewer unknowns add the products of an update one by one (UpdateTile), as the
-// one-work-group path does, so that equal rows cancel exactly and give NaN.
-constexpr int kChainBelow = 384;
+// one-work-group path does, so that equal rows cancel exactly and give NaN.  Panels of
+// one row per thread reach kSolveThreads rows; from 400 on the summed form keeps one
+// rounding of A22 per panel.
+constexpr int kChainBelow = 400;
 static_assert(kChainBelow <= kSolveThreads, "their panels are 32 columns with one row per thread");
 static_assert(kMultiMin > kSingularSlot, "x must hold the pivots and the flag");
 static_assert(kMultiMin <= kBackRows && kMultiMin <= kSolveThreads, "one row per thread and one back block below it");
