@@ -607,9 +607,11 @@ __device__ inline void back_block(double* A, long long m, int lo, int hi, int r0
         }
         __syncthreads();
         if (wave < rc) {
-            double xv = lane < bs ? L.y[wave][ib - lo + lane] : 0.0;
+            const double y0 = lane < bs ? L.y[wave][ib - lo + lane] : 0.0;
+            double xv = y0;
             const double ud = lane < bs ? L.u[lane][lane] : 1.0, uinv = 1.0 / ud;
-            if (__all(plain_exponent((unsigned)(__double_as_longlong(ud) >> 32) & 0x7fffffffu))) {
+            bool divide = !__all(plain_exponent((unsigned)(__double_as_longlong(ud) >> 32) & 0x7fffffffu));
+            if (!divide) {
                 // y / u from the reciprocal with one correction step
                 for (int i = bs - 1; i >= 0; --i) {
                     const double yi = lane_value(xv, i), u = lane_value(ud, i), v = lane_value(uinv, i);
@@ -618,7 +620,11 @@ __device__ inline void back_block(double* A, long long m, int lo, int hi, int r0
                     xi = __builtin_fma(__builtin_fma(-xi, u, yi), v, xi);
                     xv = lane == i ? xi : (lane < i ? __builtin_fma(-ui, xi, xv) : xv);
                 }
-            } else {
+                // the correction of an infinite quotient is NaN: the block is taken again
+                divide = !__all(__builtin_isfinite(xv));
+            }
+            if (divide) {
+                xv = y0;
                 for (int i = bs - 1; i >= 0; --i) {
                     const double xi = lane_value(xv, i) / lane_value(ud, i);
                     const double ui = L.u[i][lane];
