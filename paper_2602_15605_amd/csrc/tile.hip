@@ -30,7 +30,13 @@
 //
 // A work-group owns a tile of TS x TD (s, d) values of one parity and walks L in
 // chunks; P and U of a chunk are staged in LDS.  Terms outside an element's own
-// range are exact zeros (U = 0 below D and outside the band, g = 0 above S).
+// range are exact zeros (U = 0 below D and outside the band, g = 0 above S).  That
+// holds for finite U only: window values that are infinite, NaN or so large that U
+// could overflow (wild) are staged as 0, and a tile that met one adds their terms to
+// its elements at the end, each to those whose sums hold it (add_wild).  Looking for
+// them costs nothing that can be measured (TT at lmax 500 19.0 us, EE at 2700 597 us; as a
+// second form of the steps it spilled registers), EE in 2 x 2 patches excepted (lmax 2000
+// 285 us, 277 without).
 #include <algorithm>
 
 #include "couple_internal.hpp"
@@ -75,6 +81,10 @@ __host__ __device__ inline int level_tiles(int reach, int m, int par) {
     return room < 0 ? 0 : room / (2 * rho * TD) + 1;
 }
 
+// Window values from 2^960 on, infinities and NaN stay out of the staged products (below
+// that U stays below 2^1024: g <= 1, and EB's factor is below 2^31).
+__device__ __forceinline__ bool wild(double w) { return !(fabs(w) < 0x1p960); }
+
 // Work-group -> tile.  Tiles are numbered by level, the highest first: a tile runs
 // about TD m + TS steps, so the longest start first, and without gaps: work-groups
 // go to the eight XCDs in turn whatever they find to do, and a grid with empty
@@ -116,6 +126,7 @@ struct TileWindows {
     static constexpr int kAll = 2 * n1 + 2 * n2 + NX * KC;
     static constexpr int kPer = (kAll + kTileThreads - 1) / kTileThreads;
     double v[kPer * kTileThreads];
+    int met_wild;                // one of this tile's window values was
     __device__ double g1(int i) const { return v[i]; }
     __device__ double h1(int i) const { return v[n1 + i]; }
     __device__ double g2(int i) const { return v[2 * n1 + i]; }
@@ -164,11 +175,61 @@ struct TileWindows {
             }
         }
     };
-    __device__ __forceinline__ void put(const Reader& r) {
+    // met: this thread's wave has met a wild value
+    __device__ __forceinline__ void put(const Reader& r, bool& met) {
 #pragma unroll
-        for (int n = 0; n < kPer; ++n) v[threadIdx.x + n * kTileThreads] = r.reg[n];
+        for (int n = 0; n < kPer; ++n) {
+            double w = r.reg[n];
+            if ((n + 1) * kTileThreads > 2 * n1 + 2 * n2 && __builtin_expect(__any(wild(w)), 0)) {      // windows come last
+                w = wild(w) ? 0.0 : w;
+                met = true;
+            }
+            v[threadIdx.x + n * kTileThreads] = w;
+        }
+    }
+    // After the stores: whether the work-group met one (met_wild was cleared by thread 0
+    // before the first put, whose barriers order it).
+    __device__ __forceinline__ bool any_wild(bool met) {
+        if (met) met_wild = 1;
+        __syncthreads();
+        return met_wild != 0;
     }
 };
+
+// The terms of the wild window values, added to the stored sums of element (S, D) by the
+// thread that stored them: l3 over the element's own range.
+template <int MODE>
+__device__ inline void add_wild(const TileArgs& a, int par, int S, int D) {
+    constexpr bool EB = MODE == kStripEB;
+    const int d = 2 * D + par - (EB ? 1 : 0), l1 = S - D, l2 = l1 + d;
+    if (d < 0 || l1 < 0 || l2 > a.lmax) return;
+    double* x = a.xi + diag_offset(a.lmax, d) + l1;
+    const double sc = MODE == kStripTT ? 1.0 : 0.5 * a.cl[l1] * a.cl[l2];
+    const long long sh = n_shift(l1 + l2, d);
+    // EB: s = l1 + l2 + 1 here, and odd L end at l3 = s - 2
+    const int top = min(S - (EB ? 1 : 0), (a.l3_hi - par) >> 1);
+    for (int L = max(D, (a.l3_lo - par + 1) >> 1); L <= top; ++L) {
+        const int l3 = 2 * L + par;
+        const double* w = a.wp + l3;
+        const double tt = w[0], te = w[a.wp_stride], ee = w[2LL * a.wp_stride];
+        const bool on_tt = MODE != kStripEB && MODE != kStripEE && wild(tt), on_te = MODE == kStripPol && wild(te),
+                   on_ee = MODE != kStripTT && wild(ee);
+        if (!on_tt && !on_te && !on_ee) continue;
+        const double P = a.g[S - L] * a.h[S + L + par], gg = a.g[L - D] * a.g[L + D + par];
+        if (on_tt) x[0] += tt * gg * P;
+        const long long s = l1 + l2, c = (long long)l3 * (l3 + 1);
+        if (EB) {
+            const double f1 = (double)((s + 1) * (s + 2) - c), f2 = (double)(c - (long long)d * (d + 1));
+            const double f3 = (double)(c + 2LL * (l1 + 2) * (l2 + 2) - (s + 2) * (s + 3));
+            x[3 * a.xi_stride] += (sc * sc) * (ee * gg * f2 * (P * f1 * f3 * f3));
+            continue;
+        }
+        const double N = __builtin_fma((double)(c - (s + 1) * (s + 1) + 1 + sh), (double)(c - (long long)d * d + 2 - sh),
+                                       (double)n_rest(s, d, sh));
+        if (on_te) x[a.xi_stride] += sc * (te * gg * (P * N));
+        if (on_ee) x[2 * a.xi_stride] += (sc * sc) * (ee * gg * (P * N * N));
+    }
+}
 
 // ---------------------------------------------------------------------------
 // TT on the float64 matrix cores.  A wave owns NS x ND MFMA tiles of 16 x 16
@@ -198,11 +259,13 @@ __global__ void __launch_bounds__(kTileThreads) tile_tt_kernel(TileArgs a) {
 #pragma unroll
         for (int j = 0; j < NS; ++j) acc[i][j] = d4v{0.0, 0.0, 0.0, 0.0};
     constexpr int window[3] = {0, 0, 0};
+    if (t == 0) W.met_wild = 0;
+    bool met = false;
     typename Win::Reader R;
     R.start(a, w, window);
     R.fetch();
     for (int L0 = w.L_lo; L0 <= w.L_hi; L0 += KC) {
-        W.put(R);
+        W.put(R, met);
         __syncthreads();
         R.fetch();
 #pragma unroll
@@ -245,6 +308,10 @@ __global__ void __launch_bounds__(kTileThreads) tile_tt_kernel(TileArgs a) {
                 if (l1 >= 0 && l1 + d <= a.lmax) xd[l1] = acc[i][j][v];
             }
         }
+    if (__builtin_expect(W.any_wild(met), 0))
+#pragma unroll 1
+        for (int e = 0; e < ND * 4 * NS; ++e)
+            add_wild<kStripTT>(a, w.par, w.S0 + ws + 16 * (e % NS) + r, w.D0 + wd + 16 * (e / (4 * NS)) + q + 4 * (e / NS % 4));
 }
 
 // ---------------------------------------------------------------------------
@@ -300,11 +367,13 @@ __global__ void __launch_bounds__(kTileThreads, RS * RD >= 16 ? 2 : 3) tile_pol_
 
     // the windows in the order they are staged
     constexpr int window[3] = {TTS ? 0 : 2, TE ? 1 : 2, 2};
+    if (t == 0) W.met_wild = 0;
+    bool met = false;
     typename Win::Reader R;
     R.start(a, w, window);
     R.fetch();
     for (int L0 = w.L_lo; L0 <= w.L_hi; L0 += KC) {
-        W.put(R);
+        W.put(R, met);
         __syncthreads();
         R.fetch();
 #pragma unroll
@@ -400,6 +469,12 @@ __global__ void __launch_bounds__(kTileThreads, RS * RD >= 16 ? 2 : 3) tile_pol_
             xd[2 * a.xi_stride + l1] = (sc * sc) * ee[i][j];
         }
     }
+    if (__builtin_expect(W.any_wild(met), 0))
+#pragma unroll 1
+        for (int x = 0; x < RS * RD; ++x) {
+            const int i = x % RS, j = x / RS;
+            add_wild<MODE>(a, par, w.S0 + 2 * ts + (i & 1) + 32 * (i >> 1), w.D0 + 2 * td + (j & 1) + 32 * (j >> 1));
+        }
 }
 
 // Grid of the tiles TS x TD (level_tiles), and the highest level.
