@@ -64,6 +64,8 @@
 // count.  Table windows are staged in LDS in chunks of 256 steps
 // with one padding word per R entries (a lane stride of R+1 doubles is free
 // of bank conflicts).  Work items are numbered longest first.
+#include <cmath>
+
 #include "couple_internal.hpp"
 
 namespace couple {
@@ -1298,6 +1300,31 @@ hipError_t launch_strip_modes(const couple_ctx* ctx, const StripArgs& a, int lma
     return hipGetLastError();
 }
 
+// Whether the float64 tile kernels are ahead of the strips over every diagonal (same bits).
+// A band keeps the strips, whose diagonals stop exactly at the band's end.  A range of l3
+// that starts high leaves terms to the elements with l1 + l2 >= l3_lo only; `extent` is the
+// lmax of a whole triangle of as many elements (in (l1 + l2, l2 - l1) the triangle has its
+// full width from l1 + l2 = lmax on and narrows to both ends).  A patch needs enough of
+// them to fill the chip, and a range long enough to pay for its staging.  Strips / tiles, us
+// per binned call:
+//   TT + TE + EE + BB, lmax 3000   l3 0.75 .. 2 lmax (extent 2544) 816 / 792, 1 .. 2 (2121)
+//                                  491 / 566, 1.5 .. 2 (1061) 143 / 264
+//                      lmax 2500   0.75 .. 2 (2120) 499 / 486, 1 .. 2 (1768) 305 / 332
+//   EE, lmax 2000                  0.9 .. 1 64 / 58, 1 .. 1 33 / 40
+//   TT, lmax 2500                  1.5 .. 2 64 / 54, 1.75 .. 2 48 / 53, 1 .. 1 42 / 53
+bool tiles_ahead(int mode, int lmax, int l3_lo, int l3_hi) {
+    if (mode == kStripTT) return lmax >= kTileTTMid || l3_lo < lmax || l3_hi - l3_lo > lmax / 4;
+    const double m = lmax, lo = l3_lo;
+    const double extent = lo < m ? std::sqrt(m * m - 0.5 * lo * lo) : std::sqrt(2.0) * (m - 0.5 * lo);
+    if (lmax >= kTilePolBig) return extent >= 2500.0;
+    if (lmax >= kTilePolMid) return extent >= 2000.0;
+    const int from = mode == kStripPol     ? kTileMinPol
+                     : mode == kStripPolEE ? kTileMinPolEE
+                     : mode == kStripEE    ? kTileMinEE
+                                           : kTileMinEB;
+    return l3_lo < lmax && extent >= from;
+}
+
 }  // namespace
 
 hipError_t launch_strip(const couple_ctx* ctx, int lmax, int mode, int precision, int l3_lo, int l3_hi,
@@ -1319,15 +1346,7 @@ hipError_t launch_strip(const couple_ctx* ctx, int lmax, int mode, int precision
     a.l3_lo = l3_lo;
     a.l3_hi = l3_hi;
     a.band = a.dmax < lmax ? 1 : 0;
-    // float64 over every diagonal: the tile kernels from the sizes where they are
-    // ahead (same bits).  A band keeps the strips, whose diagonals stop exactly at the
-    // band's end.
-    const int tile_min = mode == kStripTT      ? 0
-                         : mode == kStripPol   ? kTileMinPol
-                         : mode == kStripPolEE ? kTileMinPolEE
-                         : mode == kStripEE    ? kTileMinEE
-                                               : kTileMinEB;
-    if (precision == COUPLE_FP64 && !a.band && lmax >= tile_min)
+    if (precision == COUPLE_FP64 && !a.band && tiles_ahead(mode, lmax, l3_lo, l3_hi))
         return launch_tile_fp64(ctx, lmax, mode, l3_lo, l3_hi, s);
     if (mode == kStripTT) {
         constexpr int RT = kStripRTT;
