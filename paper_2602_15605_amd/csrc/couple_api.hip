@@ -585,6 +585,10 @@ int matrix_masks(couple_ctx* ctx, int n_masks, const int* sorted, const int* lma
             while (g > 1 && (lmax_i[sorted[i + g - 1]] > couple::kNarrowLmax) !=
                                 (lmax_i[sorted[i]] > couple::kNarrowLmax))
                 --g;
+            // and EB's product in the order of the largest's one-mask call: one side of kTileMinEB
+            while (eb && g > 1 && precision == COUPLE_FP64 &&
+                   (lmax_i[sorted[i + g - 1]] >= couple::kTileMinEB) != (lmax_i[sorted[i]] >= couple::kTileMinEB))
+                --g;
             // FP32C's EB rows round from the lane's first row, and the group's grid puts a
             // mask's rows in lanes as the one-mask grid does only when their lmax agree mod
             // the rows per lane

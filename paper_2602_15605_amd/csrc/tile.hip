@@ -24,9 +24,10 @@
 // (TT + TE + EE) where a diagonal strip takes 8.  Odd L (EB) is the same with
 // (s+1, d+1): P f1 U (c + mu)^2, 4 operations instead of 7.
 //
-// Per element the terms are those of strip_fp64_kernel in the same order (l3
+// Per element the terms are those of the multi-mask strips in the same order (l3
 // ascending, each sum one chain of fused multiply-adds; the matrix cores'
-// float64 product is that chain too), so both give the same bits.
+// float64 product is that chain too), so both give the same bits; but for EB's
+// product, which the one-mask strips take in another order, strip_fp64_kernel's too.
 //
 // A work-group owns a tile of TS x TD (s, d) values of one parity and walks L in
 // chunks; P and U of a chunk are staged in LDS.  Terms outside an element's own
