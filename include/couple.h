@@ -352,15 +352,17 @@ int couple_threej_rows_m(couple_ctx *ctx, int m1, int m2, int n_pairs, const int
  *   work : device float64 workspace of m * (m + n_rhs) entries, overwritten.
  *   x    : device float64 [n_rhs][m], the solution.
  *   m + n_rhs <= 15840.  Gaussian elimination with partial pivoting in
- *   float64; K and rhs are not modified.  Below 192 unknowns one work-group
- *   runs it all (one kernel).  From 192 on, outer panels of 32 columns are
- *   factorised by one work-group each while the row exchanges, U12 and the
- *   trailing updates are spread over the chip; x serves as the scratch for
- *   each panel's pivots until the back substitution writes it.  A singular
- *   system (a zero pivot column) gives NaN in every entry of x.  Below 400
- *   unknowns two equal rows cancel exactly and are found so; from 400 on they
- *   leave rounding errors, and x holds finite values of no use.  Only enqueues
- *   kernels (no allocation, graph-capturable).
+ *   float64; K and rhs are not modified.  Up to 32 unknowns the matrix is
+ *   factorised by each work-group for its 256 right-hand sides (one kernel,
+ *   work is not touched); below 192, with up to 16 right-hand sides or a few
+ *   more, one work-group runs it all (one kernel).  For others, outer panels
+ *   of 32 columns are factorised by one work-group each while the row
+ *   exchanges, U12 and the trailing updates are spread over the chip; x serves
+ *   as the scratch for each panel's pivots until the back substitution writes
+ *   it.  A singular system (a zero pivot column) gives NaN in every entry of
+ *   x.  Below 400 unknowns two equal rows cancel exactly and are found so; from
+ *   400 on they leave rounding errors, and x holds finite values of no use.
+ *   Only enqueues kernels (no allocation, graph-capturable).
  * Errors (both): EINVAL (NULL ctx or pointer, misaligned pointer, sizes or
  * edges out of range), EDEVICE.
  */

@@ -26,9 +26,12 @@
 // second barrier.  Rows are not moved: a thread keeps
 // the position its row has after the exchanges.
 //
-// Small systems (m < kMultiMin) run in one work-group (master_solve_kernel),
-// with L21 and U12 staged in LDS and the trailing update on the matrix cores.
-// Larger ones split the matrix into outer panels of kOuterNB columns:
+// Systems of up to kTinyMax unknowns are one panel: each work-group factorises it for
+// its share of the right-hand sides (master_solve_tiny_kernel).
+// Small systems (m < kMultiMin and few right-hand sides) run in one work-group
+// (master_solve_kernel), with L21 and U12 staged in LDS and the trailing update on the
+// matrix cores.
+// Others split the matrix into outer panels of kOuterNB columns:
 //   solve_assemble_kernel     [K | C~] into the workspace, by columns;
 //   solve_panel_kernel        one work-group factorises NB columns (32 while the
 //                             panel has at most 1024 rows, 16, 8, 4, 2 for taller
@@ -581,60 +584,82 @@ struct UpdateTile {
     }
 };
 
-// Back substitution inside rows lo .. hi - 1 (hi - lo <= kBackRows) for rc <=
-// kBackRhs right-hand sides from column m + r0 of A on: the block's solution
-// goes back to those columns and to x.  In diagonal blocks of kBackBlock rows
-// from the bottom: one wave per right-hand side solves the diagonal block
-// (lanes over its rows), then threads over rows update the rest of the block.
+// Back substitution inside rows lo .. hi - 1 (hi - lo <= ROWS) for rc <= RHS
+// right-hand sides from column m + r0 of A on: the block's solution goes back to those
+// columns and to x.  In diagonal blocks of kBackBlock rows from the bottom: a wave solves
+// the diagonal block (lanes over its rows) for RHS / kSolveWaves right-hand sides at a
+// time, then threads over rows update the rest of the block.  load_u: false if L.u holds
+// the one diagonal block already.
 constexpr int kBackBlock = 64;
 constexpr int kBackRows = 512;
 constexpr int kBackRhs = kSolveWaves;
+template <int RHS, int ROWS>
 struct BackLds {
     double u[kBackBlock][kBackBlock + 1];    // a diagonal block of U: [column][row]
-    double y[kBackRhs][kBackRows];
+    double y[RHS][ROWS];
 };
-__device__ inline void back_block(double* A, long long m, int lo, int hi, int r0, int rc, double* x, BackLds& L) {
+template <int RHS, int ROWS>
+__device__ inline void back_block(double* A, long long m, int lo, int hi, int r0, int rc, double* x, BackLds<RHS, ROWS>& L,
+                                  bool load_u) {
+    constexpr int PER = RHS / kSolveWaves;
     const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
-    for (int e = t; e < rc * kBackRows; e += kSolveThreads) {
-        const int c = e / kBackRows, i = e % kBackRows;
+    for (int e = t; e < rc * ROWS; e += kSolveThreads) {
+        const int c = e / ROWS, i = e % ROWS;
         if (lo + i < hi) L.y[c][i] = A[(m + r0 + c) * m + lo + i];
     }
     for (int ie = hi; ie > lo; ie -= kBackBlock) {
         const int ib = max(lo, ie - kBackBlock), bs = ie - ib;
-        for (int e = t; e < kBackBlock * kBackBlock; e += kSolveThreads) {
-            const int c = e / kBackBlock, r = e % kBackBlock;
-            if (c < bs && r <= c) L.u[c][r] = A[(ib + c) * m + ib + r];
-        }
+        if (load_u)
+            for (int e = t; e < kBackBlock * kBackBlock; e += kSolveThreads) {
+                const int c = e / kBackBlock, r = e % kBackBlock;
+                if (c < bs && r <= c) L.u[c][r] = A[(ib + c) * m + ib + r];
+            }
         __syncthreads();
         if (wave < rc) {
-            const double y0 = lane < bs ? L.y[wave][ib - lo + lane] : 0.0;
-            double xv = y0;
+            double y0[PER], xv[PER];
+#pragma unroll
+            for (int p = 0; p < PER; ++p)
+                xv[p] = y0[p] = lane < bs && wave + p * kSolveWaves < rc ? L.y[wave + p * kSolveWaves][ib - lo + lane] : 0.0;
             const double ud = lane < bs ? L.u[lane][lane] : 1.0, uinv = 1.0 / ud;
             bool divide = !__all(plain_exponent((unsigned)(__double_as_longlong(ud) >> 32) & 0x7fffffffu));
             if (!divide) {
                 // y / u from the reciprocal with one correction step
                 for (int i = bs - 1; i >= 0; --i) {
-                    const double yi = lane_value(xv, i), u = lane_value(ud, i), v = lane_value(uinv, i);
+                    const double u = lane_value(ud, i), v = lane_value(uinv, i);
                     const double ui = L.u[i][lane];
-                    double xi = yi * v;
-                    xi = __builtin_fma(__builtin_fma(-xi, u, yi), v, xi);
-                    xv = lane == i ? xi : (lane < i ? __builtin_fma(-ui, xi, xv) : xv);
+#pragma unroll
+                    for (int p = 0; p < PER; ++p) {
+                        const double yi = lane_value(xv[p], i);
+                        double xi = yi * v;
+                        xi = __builtin_fma(__builtin_fma(-xi, u, yi), v, xi);
+                        xv[p] = lane == i ? xi : (lane < i ? __builtin_fma(-ui, xi, xv[p]) : xv[p]);
+                    }
                 }
                 // the correction of an infinite quotient is NaN: the block is taken again
-                divide = !__all(__builtin_isfinite(xv));
+                bool finite = true;
+#pragma unroll
+                for (int p = 0; p < PER; ++p) finite = finite && __builtin_isfinite(xv[p]);
+                divide = !__all(finite);
             }
             if (divide) {
-                xv = y0;
-                for (int i = bs - 1; i >= 0; --i) {
-                    const double xi = lane_value(xv, i) / lane_value(ud, i);
-                    const double ui = L.u[i][lane];
-                    xv = lane == i ? xi : (lane < i ? __builtin_fma(-ui, xi, xv) : xv);
+#pragma unroll
+                for (int p = 0; p < PER; ++p) {
+                    xv[p] = y0[p];
+                    for (int i = bs - 1; i >= 0; --i) {
+                        const double xi = lane_value(xv[p], i) / lane_value(ud, i);
+                        const double ui = L.u[i][lane];
+                        xv[p] = lane == i ? xi : (lane < i ? __builtin_fma(-ui, xi, xv[p]) : xv[p]);
+                    }
                 }
             }
-            if (lane < bs) {
-                L.y[wave][ib - lo + lane] = xv;
-                A[(m + r0 + wave) * m + ib + lane] = xv;
-                x[(long long)(r0 + wave) * m + ib + lane] = xv;
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+                const int c = wave + p * kSolveWaves;
+                if (lane < bs && c < rc) {
+                    L.y[c][ib - lo + lane] = xv[p];
+                    A[(m + r0 + c) * m + ib + lane] = xv[p];
+                    x[(long long)(r0 + c) * m + ib + lane] = xv[p];
+                }
             }
         }
         __syncthreads();
@@ -659,13 +684,21 @@ __device__ inline void back_block(double* A, long long m, int lo, int hi, int r0
 }
 
 constexpr int kOuterNB = 32;               // columns per outer panel
-// Systems of at least this many unknowns take the multi-work-group path (one work-group /
+// Systems of at least this many unknowns, or with more right-hand sides than
+// one_group_rhs allows, take the multi-work-group path (one work-group /
 // several, us): 176 296 / 301, 192 330 / 317, 256 496 / 437, 320 724 / 577, 383 995 / 712.
 constexpr int kMultiMin = 192;
 constexpr int kOneRows = kMultiMin + 48;   // LDS row stride of L21 in the one-work-group path: the rows and a tile's
                                            // remainder, 16 mod 32 (no conflicts)
 constexpr int kOneCols = 128;              // columns of U12 staged at a time there
 constexpr int kOneColStride = kOneCols + 16;
+
+// Right-hand sides up to which one work-group is ahead.  It takes them 16 at a time in the
+// back substitution, the others spread them over the chip but take some 40 us per outer
+// panel (one work-group / several, us): 33 unknowns with 64 of them 79 / 86; 48 with 32 84 / 86,
+// 40 92 / 89; 64 with 16 90 / 92, 24 100 / 93; 65 with 32 126 / 138, 48 141 / 142; 80 with 24
+// 144 / 140; 100 with 24 186 / 188, 32 193 / 191; 128 with 16 198 / 202, 24 226 / 203.
+inline int one_group_rhs(int m) { return m <= 48 ? 64 : m <= 64 ? 16 : m <= 80 ? 32 : 16; }
 
 // LDS of the one-work-group elimination.
 struct OneLds {
@@ -690,7 +723,7 @@ __device__ __forceinline__ void one_panel(double* A, long long m, int k0, int mr
     compose_moves(L.p, nb, L.src, L.dst, &L.moved);
 }
 
-// The whole solve in one work-group (m < kMultiMin), the matrix in the caller's
+// The whole solve in one work-group (kTinyMax < m < kMultiMin), the matrix in the caller's
 // workspace (L2).  Bound by the panels' column chains (about 1 us per column).
 __global__ void __launch_bounds__(kSolveThreads) master_solve_kernel(SolveArgs a) {
     constexpr int NB = kOuterNB;
@@ -700,7 +733,8 @@ __global__ void __launch_bounds__(kSolveThreads) master_solve_kernel(SolveArgs a
     __shared__ union Lds {
         OneLds e;
         Tile t;
-        BackLds b;
+        BackLds<kBackRhs, kMultiMin> b;
+        BackLds<2 * kBackRhs, kMultiMin> b2;
     } S;
     const int t = threadIdx.x, wave = t / kWave;
     const int m = a.m, nr = a.n_rhs, ld = m + nr;
@@ -801,14 +835,79 @@ __global__ void __launch_bounds__(kSolveThreads) master_solve_kernel(SolveArgs a
         for (long long e = t; e < (long long)nr * m; e += kSolveThreads) a.x[e] = __builtin_nan("");
         return;
     }
-    for (int r0 = 0; r0 < nr; r0 += kBackRhs) {
+    __syncthreads();
+    if (nr <= kBackRhs) {
+        back_block(A, m, 0, m, 0, nr, a.x, S.b, true);
+        return;
+    }
+    // two right-hand sides per wave take little longer than one (33 unknowns and 32 of them
+    // 67 us per call, 75 with one): a step waits for its chain
+    for (int r0 = 0; r0 < nr; r0 += 2 * kBackRhs) {
         __syncthreads();
-        back_block(A, m, 0, m, r0, min(kBackRhs, nr - r0), a.x, S.b);
+        back_block(A, m, 0, m, r0, min(2 * kBackRhs, nr - r0), a.x, S.b2, r0 == 0 || m > kBackBlock);
     }
 }
 
+// Up to kTinyMax unknowns the matrix is one panel: the first wave of every work-group
+// factorises it, straight from K, and each thread solves one right-hand side in registers.
+// No workspace.  Bound by the launch and the columns' chains (0.7 us each): 1 / 16 / 32
+// unknowns 8 / 15 / 30 us per call with up to 128 right-hand sides, 8 / 18 / 38 us with 4000.
+// The one-work-group kernel, made for larger systems, took 15 / 28 / 40 us with one and 1212 /
+// 2296 / 3327 us with 4000, which it solves eight at a time.
+constexpr int kTinyMax = kOuterNB;
+static_assert(kTinyMax >= kOuterNB, "the several work-groups keep a flag in column 0 beside the last outer panel");
+constexpr int kTinyThreads = 256;
+template <int NB>
+__global__ void __launch_bounds__(kTinyThreads) master_solve_tiny_kernel(SolveArgs a) {
+    __shared__ PivotLds<NB> P;
+    __shared__ double lu[NB][NB];                // L below the diagonal and U, by columns
+    __shared__ int src[NB], dst[NB], moved;
+    const int t = threadIdx.x, m = a.m;
+    PanelRows<NB, 1> R;
+    R.stride = kWave;
+    R.pos = t;
+    const bool in = t < m;
+    R.step[0] = in ? -1 : NB;
+#pragma unroll
+    for (int c = 0; c < NB; ++c) R.a[0][c] = in && c < m ? assembled(a, t, c) : 0.0;
+    if (t == 0) P.sing = moved = 0;
+    __syncthreads();
+    factor_rows<NB, 1>(R, m, 1, P);
+    const int q = blockIdx.x * kTinyThreads + t;
+    double* x = a.x + (long long)q * m;
+    if (P.sing) {                                // positions hold nothing of use then
+        if (q < a.n_rhs)
+            for (int i = 0; i < m; ++i) x[i] = __builtin_nan("");
+        return;
+    }
+    put_rows(R, P, m, [&](int r, int c, double v) { lu[c][r] = v; });
+    compose_moves(P, m, src, dst, &moved);
+    __syncthreads();
+    if (q >= a.n_rhs) return;
+    const double* y = a.rhs + (long long)q * m;
+    double u[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) u[i] = y[src[min(i, m - 1)]];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        if (i >= m) continue;
+#pragma unroll
+        for (int j = i + 1; j < NB; ++j) u[j] = __builtin_fma(-lu[i][j], u[i], u[j]);
+    }
+#pragma unroll
+    for (int i = NB - 1; i >= 0; --i) {
+        if (i >= m) continue;
+        u[i] /= lu[i][i];
+#pragma unroll
+        for (int j = 0; j < i; ++j) u[j] = __builtin_fma(-lu[i][j], u[i], u[j]);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+        if (i < m) x[i] = u[i];
+}
+
 // ---------------------------------------------------------------------------
-// Multi-work-group path (m >= kMultiMin).
+// Multi-work-group path (m > kTinyMax).
 constexpr int kSingularSlot = kOuterNB;    // x[kSingularSlot]: an outer panel met a zero pivot
 constexpr int kSwapCols = 64;              // columns per work-group of the swap + TRSM kernel
 constexpr int kSwapThreads = 256;
@@ -829,7 +928,7 @@ static_assert(kOuterNB <= kWave, "the swap kernel's mapping keeps two touched ro
 // rounding of A22 per panel.
 constexpr int kChainBelow = 400;
 static_assert(kChainBelow <= kSolveThreads, "their panels are 32 columns with one row per thread");
-static_assert(kMultiMin > kSingularSlot, "x must hold the pivots and the flag");
+static_assert(kTinyMax >= kSingularSlot, "x must hold the pivots and the flag");
 static_assert(kMultiMin <= kBackRows && kMultiMin <= kSolveThreads, "one row per thread and one back block below it");
 
 struct OuterArgs {
@@ -1092,7 +1191,7 @@ struct BackArgs {
 
 // kBackRhs right-hand sides per work-group.
 __global__ void __launch_bounds__(kSolveThreads) solve_back_block_kernel(BackArgs a) {
-    __shared__ BackLds L;
+    __shared__ BackLds<kBackRhs, kBackRows> L;
     const int r0 = blockIdx.x * kBackRhs, rc = min(kBackRhs, a.n_rhs - r0);
     if (a.A[a.m - 1] != 0.0) {                // singular
         for (int c = 0; c < rc; ++c)
@@ -1100,7 +1199,7 @@ __global__ void __launch_bounds__(kSolveThreads) solve_back_block_kernel(BackArg
                 a.x[(long long)(r0 + c) * a.m + i] = __builtin_nan("");
         return;
     }
-    back_block(a.A, a.m, a.lo, a.hi, r0, rc, a.x, L);
+    back_block(a.A, a.m, a.lo, a.hi, r0, rc, a.x, L, true);
 }
 
 // Rows r < lo of right-hand side blockIdx.y: y[r] -= sum over the block's columns
@@ -1181,7 +1280,17 @@ hipError_t launch_master_solve(int pol, int n, const double* K, int n_rhs, const
     a.n_rhs = n_rhs;
     a.pol = pol;
     if (a.m + n_rhs > kSolveMaxCols) return hipErrorInvalidValue;
-    if (a.m < kMultiMin) {
+    if (a.m <= kTinyMax) {
+        const dim3 grid((unsigned)((n_rhs + kTinyThreads - 1) / kTinyThreads)), block(kTinyThreads);
+        if (a.m <= 8)
+            hipLaunchKernelGGL(master_solve_tiny_kernel<8>, grid, block, 0, s, a);
+        else if (a.m <= 16)
+            hipLaunchKernelGGL(master_solve_tiny_kernel<16>, grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL(master_solve_tiny_kernel<32>, grid, block, 0, s, a);
+        return hipGetLastError();
+    }
+    if (a.m < kMultiMin && n_rhs <= one_group_rhs(a.m)) {
         hipLaunchKernelGGL(master_solve_kernel, dim3(1), dim3(kSolveThreads), 0, s, a);
         return hipGetLastError();
     }
