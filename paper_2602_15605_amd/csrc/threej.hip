@@ -24,7 +24,7 @@
 // The family kernels below extend this to (l1 l2 l3; m1 m2 m3) with small
 // magnetic numbers, (1 1 -2) and (2 2 -4) among them.
 //
-// One 256-thread work-group per (l1, l2) pair and piece of its row, threads over
+// One work-group per (l1, l2) pair and piece of its row (256 threads, short rows 64), threads over
 // l3.  The pairs are read from device memory, so the kernel itself checks them: a pair
 // outside [0, lmax_max] gives a row of NaN and reads no table.
 #include <algorithm>
@@ -35,7 +35,14 @@
 namespace couple {
 namespace {
 
-constexpr int kThreejThreads = 256;
+// Threads per work-group: 64 for rows of at most kThreejShort entries.  A row's setup runs
+// in every wave, and with four waves for 21 entries it was most of the time (20000 rows at
+// lmax 10, 256 / 64 threads: m = 0 15 / 9 us, m = 1 30 / 12, (2 2 -4) 48 / 16; at lmax 200
+// 17.5 / 13.6, 38 / 19, 63 / 26); at 801 entries 2000 rows of (2 -1 -1) take 9.9 / 13.3 us.
+constexpr int kThreejShort = 512;
+// Symbols that a thread computes before it stores any (m = 0 and the general family: one;
+// two took 13.9 against 13.5 us for 5000 rows of m = 0 at lmax 1000 and 18.5 against 17.6 us
+// for 2000 of (2 -1 -1)).
 constexpr int kThreejBatch = 2;
 // Entries of a row per block.  One block per row left the longest rows running alone at
 // the end (on average half the waves that fit): with the kernels below 2000 rows at lmax
@@ -43,9 +50,18 @@ constexpr int kThreejBatch = 2;
 // entries: 52 and 79 us, the row's setup weighs more; 8192: 58 and 65 us).  Plain stores:
 // past the caches (nontemporal) the same rows took 56 and 64 us.
 constexpr int kThreejPiece = 2048;
+// Results beyond the memory-side cache take longer pieces: first pieces of all rows are
+// written before second ones, and memory likes long runs (entries 2048 / 4096 / 8192, 20000
+// rows at lmax 2000: m = 1 153 / 137 / 137 us, (2 -1 -1) 219 / 185 / 185; 10000 at lmax 4000:
+// 147 / 139 / 145 and 212 / 210 / 191).
+constexpr double kThreejPastBytes = 256e6;
+constexpr int kThreejPastPiece = 4096, kFamilyPastPiece = 8192;
 
-inline dim3 piece_grid(int n_pairs, long long stride) {
-    return dim3((unsigned)n_pairs, (unsigned)std::min((stride + kThreejPiece - 1) / kThreejPiece, 1024LL));
+inline int row_piece(int n_pairs, long long stride, int past) {
+    return 8.0 * n_pairs * (double)stride > kThreejPastBytes ? past : kThreejPiece;
+}
+inline dim3 piece_grid(int n_pairs, long long stride, int piece) {
+    return dim3((unsigned)n_pairs, (unsigned)std::min((stride + piece - 1) / piece, 1024LL));
 }
 
 struct ThreejArgs {
@@ -57,10 +73,12 @@ struct ThreejArgs {
     double* out;                 // [n_pairs][stride]
     long long stride;
     int lmax_max;
+    int piece;                   // entries per block
     int m;
 };
 
 // Zeros in entries i .. end - 1 of a row, 16 bytes per store.
+template <int T>
 __device__ inline void put_zeros(double* row, long long i, long long end) {
     typedef double d2v __attribute__((ext_vector_type(2)));
     if (i < end && (reinterpret_cast<uintptr_t>(row + i) & 15)) {
@@ -69,7 +87,7 @@ __device__ inline void put_zeros(double* row, long long i, long long end) {
     }
     const long long pairs = end > i ? (end - i) / 2 : 0;
     d2v* out = reinterpret_cast<d2v*>(row + i);
-    for (long long q = threadIdx.x; q < pairs; q += kThreejThreads)
+    for (long long q = threadIdx.x; q < pairs; q += T)
         out[q] = d2v{0.0, 0.0};
     if (threadIdx.x == 0 && i + 2 * pairs < end) row[end - 1] = 0.0;
 }
@@ -77,27 +95,26 @@ __device__ inline void put_zeros(double* row, long long i, long long end) {
 // Runs `entries(lo, hi)` for the pieces of this block's row that hold some of its n
 // symbols, and writes NaN (a degree out of range) or zeros elsewhere.  Pieces start at
 // even entries.
-template <class Entries>
-__device__ inline void each_piece(double* row, long long n, long long stride, bool nan, Entries entries) {
-    for (long long lo = (long long)blockIdx.y * kThreejPiece; lo < stride; lo += (long long)gridDim.y * kThreejPiece) {
-        const long long end = min(lo + kThreejPiece, stride), hi = min(n, end);
+template <int T, class Entries>
+__device__ inline void each_piece(double* row, long long n, long long stride, int piece, bool nan, Entries entries) {
+    for (long long lo = (long long)blockIdx.y * piece; lo < stride; lo += (long long)gridDim.y * piece) {
+        const long long end = min(lo + piece, stride), hi = min(n, end);
         if (nan) {
-            for (long long i = lo + threadIdx.x; i < end; i += kThreejThreads) row[i] = __builtin_nan("");
+            for (long long i = lo + threadIdx.x; i < end; i += T) row[i] = __builtin_nan("");
             continue;
         }
-        put_zeros(row, max(lo, hi), end);
+        put_zeros<T>(row, max(lo, hi), end);
         if (lo < hi) entries((int)lo, (int)hi);
     }
 }
 
-// The factor shared by a whole row: m = 1: -1 / (2 sqrt(a b)); m = 2: c_l1 c_l2 / 2.
+// The factor shared by a whole row of degrees >= m: m = 1: -1 / (2 sqrt(a b)); m = 2: c_l1 c_l2 / 2.
 __device__ inline double row_factor(const ThreejArgs& a, long long l1, long long l2) {
-    if (a.m == 1) return (l1 < 1 || l2 < 1) ? 0.0 : -0.5 / sqrt((double)(l1 * (l1 + 1)) * (double)(l2 * (l2 + 1)));
-    if (a.m == 2) return (l1 < 2 || l2 < 2) ? 0.0 : 0.5 * a.cl[l1] * a.cl[l2];
-    return 1.0;
+    if (a.m == 1) return -0.5 / sqrt((double)(l1 * (l1 + 1)) * (double)(l2 * (l2 + 1)));
+    return 0.5 * a.cl[l1] * a.cl[l2];
 }
 
-// Each thread computes kThreejBatch symbols of its row before it stores any,
+// For m = 1, 2 each thread computes kThreejBatch symbols of its row before it stores any,
 // so their table reads are in flight together.  For m = 0 the symbols of odd
 // L vanish; a row starts at L = 2 max(l1, l2), so its even entries are the
 // even-L ones, and each thread takes a pair of entries: it evaluates the even
@@ -115,34 +132,25 @@ __device__ inline double row_factor(const ThreejArgs& a, long long l1, long long
 // them the root; with 64-bit integers, both parities' factors and two roots per
 // symbol 2000 rows at lmax 6000 took 57 us, now 37 us (115 MB of results and 77 MB of
 // zeros: 5.2 TB/s); 200 rows at lmax 16000 67 us, now 16 us.
-__global__ void __launch_bounds__(kThreejThreads) threej_rows_kernel(ThreejArgs a) {
+template <int T>
+__global__ void __launch_bounds__(T) threej_rows_kernel(ThreejArgs a) {
     const long long p = blockIdx.x;
     const int l1 = a.l1[p], l2 = a.l2[p];
     double* row = a.out + p * a.stride;
     const bool nan = l1 < 0 || l2 < 0 || l1 > a.lmax_max || l2 > a.lmax_max;
     const int jmin = l1 > l2 ? l1 - l2 : l2 - l1;
     if (nan || min(l1, l2) < a.m) {           // a selection rule |m| <= l fails: zeros
-        each_piece(row, 0, a.stride, nan, [](int, int) {});
+        each_piece<T>(row, 0, a.stride, a.piece, nan, [](int, int) {});
         return;
     }
     const int n = l1 + l2 - jmin + 1;
     if (a.m == 0) {
-        each_piece(row, n, a.stride, false, [&](int lo, int hi) {
-            for (int q0 = lo + 2 * threadIdx.x; q0 < hi; q0 += 2 * kThreejThreads * kThreejBatch) {
-                double v[kThreejBatch];
-#pragma unroll
-                for (int q = 0; q < kThreejBatch; ++q) {
-                    const int i = min(q0 + 2 * q * kThreejThreads, (hi - 1) & ~1);
-                    const int P = (l1 + l2 + jmin + i) / 2;
-                    const double r = sqrt(a.g[P - l1] * a.g[P - l2] * a.g[P - jmin - i] * a.h[P]);
-                    v[q] = (P & 1) ? -r : r;
-                }
-#pragma unroll
-                for (int q = 0; q < kThreejBatch; ++q) {
-                    const int i = q0 + 2 * q * kThreejThreads;
-                    if (i < hi) row[i] = v[q];
-                    if (i + 1 < hi) row[i + 1] = 0.0;
-                }
+        each_piece<T>(row, n, a.stride, a.piece, false, [&](int lo, int hi) {
+            for (int i = lo + 2 * threadIdx.x; i < hi; i += 2 * T) {
+                const int P = (l1 + l2 + jmin + i) / 2;
+                const double r = sqrt(a.g[P - l1] * a.g[P - l2] * a.g[P - jmin - i] * a.h[P]);
+                row[i] = (P & 1) ? -r : r;
+                if (i + 1 < hi) row[i + 1] = 0.0;
             }
         });
         return;
@@ -156,13 +164,13 @@ __global__ void __launch_bounds__(kThreejThreads) threej_rows_kernel(ThreejArgs 
     const long long dd = (long long)l2 - l1;
     const double s1 = (double)((s + 1) * (s + 2)), d1 = (double)(dd * (dd + 1));
     const double mu = (double)(2LL * (l1 + 2) * (l2 + 2) - (s + 2) * (s + 3));
-    each_piece(row, n, a.stride, false, [&](int lo, int hi) {
-        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += kThreejThreads * kThreejBatch) {
+    each_piece<T>(row, n, a.stride, a.piece, false, [&](int lo, int hi) {
+        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += T * kThreejBatch) {
             double v[kThreejBatch];
 #pragma unroll
             for (int q = 0; q < kThreejBatch; ++q) {
                 // entries past the piece repeat its last one of this parity, unstored
-                const int i = min(i0 + q * kThreejThreads, hi - 1 - ((hi - 1 - i0) & 1));
+                const int i = min(i0 + q * T, hi - 1 - ((hi - 1 - i0) & 1));
                 const int l3 = jmin + i, L = l1 + l2 + l3;
                 // (l1, l2 + odd, l3; 0 0 0)^2: odd L has |l1 - l2 - 1| <= l3 < l1 + l2
                 const int P = (L + odd) / 2;
@@ -181,11 +189,51 @@ __global__ void __launch_bounds__(kThreejThreads) threej_rows_kernel(ThreejArgs 
             }
 #pragma unroll
             for (int q = 0; q < kThreejBatch; ++q) {
-                const int i = i0 + q * kThreejThreads;
+                const int i = i0 + q * T;
                 if (i < hi) row[i] = v[q];
             }
         }
     });
+}
+
+// Rows of m = 0 of these many entries that go past the memory-side cache: one block per
+// row, symbols and zeros in one pass, and no more than six work-groups per compute unit.
+// How the rows fall into memory decides here, not the instructions (eight work-groups per
+// compute unit take up to a fifth longer): threej_rows_kernel / this one take 75 / 67 us for
+// 30000 rows at lmax 800, 70 / 64 for 25000 at 900, 61 / 58 for 20000 at 1000, 77 / 72 at 1200,
+// but 75 / 85 for 40000 at 600 and 136 / 140 for 20000 at 2000.
+constexpr int kZeroRowsFrom = 1400, kZeroRowsTo = 2600;
+constexpr int kZeroRowsLds = 26500;              // six work-groups per compute unit
+__global__ void __launch_bounds__(256) threej_zero_rows_kernel(ThreejArgs a) {
+    constexpr int kBatch = 4;
+    const long long p = blockIdx.x, l1 = a.l1[p], l2 = a.l2[p];
+    double* row = a.out + p * a.stride;
+    if (l1 < 0 || l2 < 0 || l1 > a.lmax_max || l2 > a.lmax_max) {
+        for (long long i = threadIdx.x; i < a.stride; i += 256) row[i] = __builtin_nan("");
+        return;
+    }
+    const long long jmin = l1 > l2 ? l1 - l2 : l2 - l1, n = l1 + l2 - jmin + 1;
+    auto x000 = [&](long long l3) {
+        const long long L = l1 + l2 + l3;
+        if ((L & 1) || l3 < jmin || l3 > l1 + l2) return 0.0;
+        const long long P = L / 2;
+        const double r = sqrt(a.g[P - l1] * a.g[P - l2] * a.g[P - l3] * a.h[P]);
+        return (P & 1) ? -r : r;
+    };
+    for (long long q0 = threadIdx.x; 2 * q0 < a.stride; q0 += 256 * kBatch) {
+        double v[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+            const long long i = 2 * (q0 + 256 * q);
+            v[q] = i < n ? x000(jmin + i) : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+            const long long i = 2 * (q0 + 256 * q);
+            if (i < a.stride) row[i] = v[q];
+            if (i + 1 < a.stride) row[i + 1] = 0.0;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -220,8 +268,6 @@ __global__ void __launch_bounds__(kThreejThreads) threej_rows_kernel(ThreejArgs 
 // exactly in 128-bit integers (below 2^118 for l <= 16384; A, B, C and s, t
 // are even, so the halvings are exact), so the roundings are its conversion,
 // the table product, D_ab and two square roots: no cancellation anywhere.
-// Even and odd L alternate along a row; both numerators are formed and one is
-// kept per lane, as in symbol() above.
 
 struct FamilyArgs {
     const double* g;
@@ -231,6 +277,7 @@ struct FamilyArgs {
     double* out;                 // [n_pairs][stride]
     long long stride;
     int lmax_max;
+    int piece;                   // entries per block
     int rot;                     // (x, y, z) = (l1, l2, l3) rotated left by rot
     int flip;                    // 1: times (-1)^L
 };
@@ -306,26 +353,17 @@ __device__ inline double family_symbol(const FamilyArgs& f, long long l1, long l
 }
 
 // The general kernel: rows whose l3 is not the column z.
-template <int AB>
-__global__ void __launch_bounds__(kThreejThreads) threej_family_kernel(FamilyArgs f) {
+template <int AB, int T>
+__global__ void __launch_bounds__(T) threej_family_kernel(FamilyArgs f) {
     const long long p = blockIdx.x;
     const int l1 = f.l1[p], l2 = f.l2[p];
     double* row = f.out + p * f.stride;
     const bool nan = l1 < 0 || l2 < 0 || l1 > f.lmax_max || l2 > f.lmax_max;
     const long long jmin = l1 > l2 ? l1 - l2 : l2 - l1;
-    each_piece(row, nan ? 0 : (long long)l1 + l2 - jmin + 1, f.stride, nan, [&](int lo, int hi) {
-        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += kThreejThreads * kThreejBatch) {
-            double v[kThreejBatch];
-#pragma unroll
-            for (int q = 0; q < kThreejBatch; ++q) {
-                const int i = i0 + q * kThreejThreads;
-                v[q] = i < hi ? family_symbol<AB>(f, l1, l2, jmin + i) : 0.0;
-            }
-#pragma unroll
-            for (int q = 0; q < kThreejBatch; ++q) {
-                const int i = i0 + q * kThreejThreads;
-                if (i < hi) row[i] = v[q];
-            }
+    each_piece<T>(row, nan ? 0 : (long long)l1 + l2 - jmin + 1, f.stride, f.piece, nan, [&](int lo, int hi) {
+        for (int i = lo + threadIdx.x; i < hi; i += T) {
+            const double v = i < hi ? family_symbol<AB>(f, l1, l2, jmin + i) : 0.0;
+            if (i < hi) row[i] = v;
         }
     });
 }
@@ -349,15 +387,15 @@ __device__ inline unsigned __int128 mul_u32(unsigned __int128 v, unsigned c) {
 // What bounds it: about 150 instructions per symbol.  2000 rows of (2 2 -4) at lmax 6000
 // take 54 us, with the full 128-bit polynomials of both parities and two roots per
 // symbol 131 us; (1 1 -2) 43 us, before 78 us.
-template <int AB>
-__global__ void __launch_bounds__(kThreejThreads) threej_family_row_kernel(FamilyArgs f) {
+template <int AB, int T>
+__global__ void __launch_bounds__(T) threej_family_row_kernel(FamilyArgs f) {
     constexpr int a = AB / 3, b = AB % 3;
     const long long p = blockIdx.x;
     const int l1 = f.l1[p], l2 = f.l2[p];
     double* row = f.out + p * f.stride;
     const bool nan = l1 < 0 || l2 < 0 || l1 > f.lmax_max || l2 > f.lmax_max;
     if (nan || l1 < a || l2 < b) {
-        each_piece(row, 0, f.stride, nan, [](int, int) {});
+        each_piece<T>(row, 0, f.stride, f.piece, nan, [](int, int) {});
         return;
     }
     const int jmin = l1 > l2 ? l1 - l2 : l2 - l1, n = l1 + l2 - jmin + 1;
@@ -379,12 +417,12 @@ __global__ void __launch_bounds__(kThreejThreads) threej_family_row_kernel(Famil
     for (int k = 0; k < a; ++k) dab *= (double)(A - k * (k + 1));
 #pragma unroll
     for (int k = 0; k < b; ++k) dab *= (double)(B - k * (k + 1));
-    each_piece(row, n, f.stride, false, [&](int lo, int hi) {
-        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += kThreejThreads * kThreejBatch) {
+    each_piece<T>(row, n, f.stride, f.piece, false, [&](int lo, int hi) {
+        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += T * kThreejBatch) {
             double v[kThreejBatch];
 #pragma unroll
             for (int q = 0; q < kThreejBatch; ++q) {
-                const int i = min(i0 + q * kThreejThreads, hi - 1 - ((hi - 1 - i0) & 1));
+                const int i = min(i0 + q * T, hi - 1 - ((hi - 1 - i0) & 1));
                 const int l3 = jmin + i, L = l1 + l2 + l3, P = (L + 1) / 2;
                 const int p1 = P - l1, p2 = P - l2, p3 = P - l3;
                 const int C = l3 * (l3 + 1);
@@ -401,7 +439,7 @@ __global__ void __launch_bounds__(kThreejThreads) threej_family_row_kernel(Famil
             }
 #pragma unroll
             for (int q = 0; q < kThreejBatch; ++q) {
-                const int i = i0 + q * kThreejThreads;
+                const int i = i0 + q * T;
                 if (i < hi) row[i] = v[q];
             }
         }
@@ -422,13 +460,20 @@ hipError_t launch_threej_family(const couple_ctx* ctx, int rot, int flip, int a,
     f.lmax_max = ctx->lmax_max;
     f.rot = rot;
     f.flip = flip;
-    const dim3 grid = piece_grid(n_pairs, stride), block(kThreejThreads);
-    auto launch = [&](auto ab) {
-        constexpr int AB = decltype(ab)::value;
+    f.piece = row_piece(n_pairs, stride, kFamilyPastPiece);
+    const dim3 grid = piece_grid(n_pairs, stride, f.piece);
+    auto launch_threads = [&](auto ab, auto threads) {
+        constexpr int AB = decltype(ab)::value, T = decltype(threads)::value;
         if (rot == 0)
-            hipLaunchKernelGGL(threej_family_row_kernel<AB>, grid, block, 0, s, f);
+            hipLaunchKernelGGL((threej_family_row_kernel<AB, T>), grid, dim3(T), 0, s, f);
         else
-            hipLaunchKernelGGL(threej_family_kernel<AB>, grid, block, 0, s, f);
+            hipLaunchKernelGGL((threej_family_kernel<AB, T>), grid, dim3(T), 0, s, f);
+    };
+    auto launch = [&](auto ab) {
+        if (stride <= kThreejShort)
+            launch_threads(ab, std::integral_constant<int, 64>());
+        else
+            launch_threads(ab, std::integral_constant<int, 256>());
     };
     switch (3 * a + b) {
     case 0: launch(std::integral_constant<int, 0>()); break;
@@ -457,7 +502,14 @@ hipError_t launch_threej_rows(const couple_ctx* ctx, int m, int n_pairs, const i
     a.stride = stride;
     a.lmax_max = ctx->lmax_max;
     a.m = m;
-    hipLaunchKernelGGL(threej_rows_kernel, piece_grid(n_pairs, stride), dim3(kThreejThreads), 0, s, a);
+    a.piece = row_piece(n_pairs, stride, kThreejPastPiece);
+    const dim3 grid = piece_grid(n_pairs, stride, a.piece);
+    if (m == 0 && a.piece != kThreejPiece && stride >= kZeroRowsFrom && stride <= kZeroRowsTo)
+        hipLaunchKernelGGL(threej_zero_rows_kernel, dim3((unsigned)n_pairs), dim3(256), kZeroRowsLds, s, a);
+    else if (stride <= kThreejShort)
+        hipLaunchKernelGGL(threej_rows_kernel<64>, grid, dim3(64), 0, s, a);
+    else
+        hipLaunchKernelGGL(threej_rows_kernel<256>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
