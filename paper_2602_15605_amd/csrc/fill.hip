@@ -28,9 +28,12 @@ constexpr int kFillWays = 8;     // threads per tile column: a thread's T / kFil
 // one diagonal after another, 52.7), 500 44.0 / 44.0 / 47.5 (66.3), 1000 89 / 87 / 87
 // (104), 2000 331 / 321 / 317 (338); TT at lmax 3000 323 / 317 / 312 (324).
 constexpr long long kFill32Entries = 600000, kFill64Entries = 6000000;
-// fill_large_kernel from here on (400 MB, above what the memory-side cache holds): plain
-// stores / past the caches at lmax 4500, four matrices, 2916 / 2830 us; lmax 3000 922 / 933.
-constexpr long long kFillPastEntries = 50000000;
+// fill_large_kernel from here on (above what the memory-side cache holds): this kernel / it,
+// four matrices of one mask at lmax 3100 115 / 125 us, 3300 (43.6M entries) 136 / 137, 3500
+// 159 / 152, 4500 269 / 249; TT at 6000 (36M) 111 / 114, 6300 127 / 125, 7000 168 / 153.
+// Several masks of small lmax keep this kernel longer (12 of lmax 1000, 48M, 214 us, before
+// 382).
+constexpr long long kFillPastEntries = 42000000, kFillPastEntriesMasks = 50000000;
 constexpr int kT = 64;           // the largest tile edge
 constexpr int kFillThreads = 512;  // 8 waves per tile: more stores in flight per LDS tile
 
@@ -124,7 +127,7 @@ __device__ inline void pair_by_rows(int t, int n, int* I, int* J) {
     *J = i + rem;
 }
 
-// Launches of at least kFillPastEntries: 64 x 64 tiles, 512 threads, few registers, the
+// Launches of at least kFillPastEntries (kFillPastEntriesMasks): 64 x 64 tiles, 512 threads, few registers, the
 // diagonals of a tile one after another, stores past the caches.  Bound by the memory's
 // writes (at lmax 6000, four matrices, 1.6 GB in 0.463 ms; fill_kernel<64> 0.476, the 32
 // masks of lmax 500 .. 4000 14.76 against 14.92 ms per call).
@@ -361,7 +364,7 @@ hipError_t launch_fill_jobs(const FillJob* jobs, int n_jobs, const int* spec_src
     for (int j = 0; j < n_jobs; ++j) entries += (jobs[j].lmax + 1LL) * (jobs[j].lmax + 1LL) * n_out;
     const int T = entries < kFill32Entries ? 16 : entries < kFill64Entries ? 32 : kT;
     const dim3 grid = blocks(T);
-    if (entries >= kFillPastEntries)
+    if (entries >= (n_jobs == 1 ? kFillPastEntries : kFillPastEntriesMasks))
         hipLaunchKernelGGL(fill_large_kernel, grid, dim3(kFillThreads), 0, s, a);
     else if (T == 16)
         hipLaunchKernelGGL(fill_kernel<16>, grid, dim3(kFillWays * 16), 0, s, a);
