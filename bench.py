@@ -27,12 +27,23 @@ sys.path.insert(0, ROOT)
 # fp32 128 lanes/clk/CU (157.3 TFLOP/s), reached on gfx950 by plain (non-packed) fp32 VALU ops.
 PEAK_VALU_TFLOPS = {"fp64": 78.6, "fp32c": 157.3}
 PEAK_HBM_GBS = 8000.0
-# Useful arithmetic per even-L triple as the strip kernels evaluate it (FMA = 2 FLOP): the
-# (0 0 0)^2 factors g(k) g(d+k) W'(l3) are wave-uniform per step and folded into U(k), so
-# per triple TT is P = g h (1) and one FMA (2); TE/EE are N' (one add and one FMA: 3),
-# y = P N' and z = y N' (2) and two FMA accumulations (4).  This is the roofline's
-# achieved rate.
-FLOP_PER_TRIPLE_POL = 12
+# The l3-reduction kernel of a call for TT, TE, EE and BB, and its useful arithmetic per
+# even-L triple (FMA = 2 FLOP), the roofline's achieved rate.
+#   fp32c, strip_fp32c_kernel: the (0 0 0)^2 factors g(k) g(d+k) W'(l3) are wave-uniform per
+#     step and folded into U(k), so TT is P = g h (1) and one FMA (2); TE/EE are N' (one add
+#     and one FMA: 3), y = P N' and z = y N' (2) and two FMA accumulations (4): 12.
+#   fp64, tile_pol_kernel: P is formed once per (l3, l1 + l2), N' is one FMA (2): 10.  Below
+#     lmax 1400 strip_fp64_kernel, 12 as above.
+TILE_FROM = 1400
+
+
+def reduction_kernel(prec: str, lmax: int):
+    """(kernel, FLOP per triple) of the four-spectra l3 reduction."""
+    if prec == "fp64" and lmax >= TILE_FROM:
+        return "tile_pol_kernel", 10
+    return "strip_%s_kernel" % prec, 12
+
+
 # The method's count with X^2 formed per triple (three multiplies), as the paper's
 # evaluation of eq. 000_sq_main does: TT 5 + TE/EE 11.  Reported as the effective rate.
 FLOP_PER_TRIPLE_PAPER = 16
@@ -42,11 +53,11 @@ FLOP_PER_TRIPLE_BAND = 10
 
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "strip_pol4_lmax6000_traffic.md")
-STRIP_SOURCES = [os.path.join(ROOT, "paper_2602_15605_amd", "csrc", f) for f in ("strip.hip", "strip_params.hpp")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2602_15605_amd", "csrc", f) for f in ("strip.hip", "strip_params.hpp", "tile.hip")]
 
 
 def measured_traffic(kernel: str):
-    """HBM bytes per launch of a strip kernel from the committed FETCH_SIZE / WRITE_SIZE
+    """HBM bytes per launch of a reduction kernel from the committed FETCH_SIZE / WRITE_SIZE
     summary, or None when it is missing or the kernel source changed since it was taken."""
     import hashlib
     try:
@@ -54,7 +65,7 @@ def measured_traffic(kernel: str):
     except OSError:
         return None
     h = hashlib.sha256()
-    for path in STRIP_SOURCES:
+    for path in KERNEL_SOURCES:
         with open(path, "rb") as f:
             h.update(f.read())
     value = digest = None
@@ -293,10 +304,10 @@ def run_extras(torch, couple, synth, args):
         kms = {k: prof[k][0] / steps for k in ("scale_windows", "strip", "fill")}
         # TT and EE per triple (no TE): P, the TT FMA, the t step, the N' FMA, two multiplies, the EE FMA
         tflops = FLOP_PER_TRIPLE_BAND * T_band * 8 / (kms["strip"] * 1e-3) / 1e12
-        # the multi-mask strip forms P, N' (3 FLOP; 4 in the wide float64 form) and the two
-        # products once per term for its 4 masks, then 2 FMAs per mask: executed FLOP per
+        # the multi-mask strip forms P, N' (3 FLOP: one add and one FMA) and the two products
+        # once per term for its 4 masks, then 2 FMAs per mask: executed FLOP per
         # mask-triple = 4 + shared / 4
-        shared = 1 + (3 if prec == "fp32c" else 4) + 2
+        shared = 1 + 3 + 2
         executed = 4 + shared / 4.0
         xtflops = executed * T_band * 8 / (kms["strip"] * 1e-3) / 1e12
         peak = PEAK_VALU_TFLOPS[prec]
@@ -490,7 +501,7 @@ def main():
         ms_step = ev0.elapsed_time(ev1) / args.steps
         strip_ms, strip_n = prof["strip"]
         strip_avg = strip_ms / max(1, strip_n)
-        flops = FLOP_PER_TRIPLE_POL * T
+        flops = reduction_kernel(prec, lmax)[1] * T
         r = {
             "ms_per_step": ms_step,
             "ms_per_step_std": float(per_step.std(ddof=1)) if args.steps > 1 else 0.0,
@@ -543,7 +554,8 @@ def main():
     head = "fp32c" if "ms_per_step" in results.get("fp32c", {}) else "fp64"
     h = results[head]
     strip_avg = h["kernel_ms"]["strip"]
-    achieved = FLOP_PER_TRIPLE_POL * T / (strip_avg * 1e-3) / 1e12
+    kernel, flop_per_triple = reduction_kernel(head, lmax)
+    achieved = flop_per_triple * T / (strip_avg * 1e-3) / 1e12
     line = {
         "metric": "K elements/s at lmax=6000 TT+pol, FP32-comp/MFMA vs FP64 plain, max rel err",
         "value": h["k_elements_per_s"],
@@ -564,8 +576,8 @@ def main():
                    "triples": T, "elements_per_step": n_el},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_VALU_TFLOPS[head], "unit": "TFLOP/s",
                      "frac": achieved / PEAK_VALU_TFLOPS[head],
-                     "traffic": measured_traffic("strip_%s_kernel" % head),
-                     "kernel": "strip_%s_kernel (l3 reduction)" % head, "flop_per_triple": FLOP_PER_TRIPLE_POL,
+                     "traffic": measured_traffic(kernel),
+                     "kernel": "%s (l3 reduction)" % kernel, "flop_per_triple": flop_per_triple,
                      "effective": {"flop_per_triple": FLOP_PER_TRIPLE_PAPER,
                                    "achieved": FLOP_PER_TRIPLE_PAPER * T / (strip_avg * 1e-3) / 1e12,
                                    "frac": FLOP_PER_TRIPLE_PAPER * T / (strip_avg * 1e-3) / 1e12

@@ -89,7 +89,8 @@ hipError_t launch_window_exponents(const couple_ctx* ctx, int n, hipStream_t s, 
 hipError_t launch_strip(const couple_ctx* ctx, int lmax, int mode, int precision, int l3_lo,
                         int l3_hi, hipStream_t s);
 // The same sums in float64 over the whole triangle (every diagonal of lmax), as a
-// matrix product (tile.hip); launch_strip calls it, and the bits are the strip kernels'.
+// matrix product (tile.hip); launch_strip calls it where tiles are ahead, and
+// launch_strip_masks gives the same bits there.
 hipError_t launch_tile_fp64(const couple_ctx* ctx, int lmax, int mode, int l3_lo, int l3_hi, hipStream_t s);
 // Masks one launch_strip_masks call takes in a mode.
 int strip_masks_per_launch(int mode, int precision);

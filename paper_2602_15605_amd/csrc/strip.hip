@@ -1303,7 +1303,8 @@ hipError_t launch_strip_modes(const couple_ctx* ctx, const StripArgs& a, int lma
     return hipGetLastError();
 }
 
-// Whether the float64 tile kernels are ahead of the strips over every diagonal (same bits).
+// Whether the float64 tile kernels are ahead of the strips over every diagonal (same bits
+// but for the order of EB's product).
 // A band keeps the strips, whose diagonals stop exactly at the band's end.  A range of l3
 // that starts high leaves terms to the elements with l1 + l2 >= l3_lo only; `extent` is the
 // lmax of a whole triangle of as many elements (in (l1 + l2, l2 - l1) the triangle has its

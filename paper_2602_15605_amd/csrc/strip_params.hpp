@@ -77,11 +77,14 @@ constexpr int kNarrowLmax = 8000;
 // Small triangles leave the tiles' longer patches without enough waves; TT's stay
 // ahead at every size.
 constexpr int kTileMinPol = 1400, kTileMinPolEE = 1150, kTileMinEE = 1250, kTileMinEB = 1000;
-// lmax from which a thread takes 4 x 2 and 4 x 4 (s, d) values instead of 2 x 2 (TT +
-// TE + EE at 2000 / 2500 / 3000: 443 / 804 / 1358 us with 2 x 2, 502 / 788 / 1277 with
-// 4 x 2, 643 / 935 / 1271 with 4 x 4), and a wave of the TT kernel 2 x 2 and 4 x 2 MFMA
-// tiles instead of one (2000 / 3000 / 10^4: 110 / 286 / 8499 us with one, 153 / 276 / 6785
-// with 2 x 2, 209 / 361 / 6652 with 4 x 2).
+// lmax from which a thread takes 4 x 2 and 4 x 4 (s, d) values instead of 2 x 2 (us at lmax
+// 2200 / 2400 / 2800 / 3000 with 2 x 2, 4 x 2 and 4 x 4:
+//   TT + TE + EE   547 703 1098 1339,   566 674 1028 1253,   725 836 1074 1254
+//   TT + EE        437 559  862 1042,   463 551  827 1000,   586 674  850  982
+//   EE             361 457  702  848,   375 440  667  803,   469 537  673  777
+//   EB             327 426  642  776,   366 425  630  760,   450 513  636  732),
+// and a wave of the TT kernel 2 x 2 and 4 x 2 MFMA tiles instead of one (2000 / 3000 /
+// 10^4: 110 / 286 / 8499 us with one, 153 / 276 / 6785 with 2 x 2, 209 / 361 / 6652 with 4 x 2).
 constexpr int kTilePolMid = 2400, kTilePolBig = 2900;
 constexpr int kTileTTMid = 2700, kTileTTBig = 6000;
 
