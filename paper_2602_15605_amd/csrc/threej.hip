@@ -57,9 +57,7 @@ constexpr int kThreejPiece = 2048;
 constexpr double kThreejPastBytes = 256e6;
 constexpr int kThreejPastPiece = 4096, kFamilyPastPiece = 8192;
 
-inline int row_piece(int n_pairs, long long stride, int past) {
-    return 8.0 * n_pairs * (double)stride > kThreejPastBytes ? past : kThreejPiece;
-}
+inline bool past_cache(int n_pairs, long long stride) { return 8.0 * n_pairs * (double)stride > kThreejPastBytes; }
 inline dim3 piece_grid(int n_pairs, long long stride, int piece) {
     return dim3((unsigned)n_pairs, (unsigned)std::min((stride + piece - 1) / piece, 1024LL));
 }
@@ -73,7 +71,6 @@ struct ThreejArgs {
     double* out;                 // [n_pairs][stride]
     long long stride;
     int lmax_max;
-    int piece;                   // entries per block
     int m;
 };
 
@@ -95,10 +92,10 @@ __device__ inline void put_zeros(double* row, long long i, long long end) {
 // Runs `entries(lo, hi)` for the pieces of this block's row that hold some of its n
 // symbols, and writes NaN (a degree out of range) or zeros elsewhere.  Pieces start at
 // even entries.
-template <int T, class Entries>
-__device__ inline void each_piece(double* row, long long n, long long stride, int piece, bool nan, Entries entries) {
-    for (long long lo = (long long)blockIdx.y * piece; lo < stride; lo += (long long)gridDim.y * piece) {
-        const long long end = min(lo + piece, stride), hi = min(n, end);
+template <int T, int PIECE, class Entries>
+__device__ inline void each_piece(double* row, long long n, long long stride, bool nan, Entries entries) {
+    for (long long lo = (long long)blockIdx.y * PIECE; lo < stride; lo += (long long)gridDim.y * PIECE) {
+        const long long end = min(lo + PIECE, stride), hi = min(n, end);
         if (nan) {
             for (long long i = lo + threadIdx.x; i < end; i += T) row[i] = __builtin_nan("");
             continue;
@@ -132,7 +129,7 @@ __device__ inline double row_factor(const ThreejArgs& a, long long l1, long long
 // them the root; with 64-bit integers, both parities' factors and two roots per
 // symbol 2000 rows at lmax 6000 took 57 us, now 37 us (115 MB of results and 77 MB of
 // zeros: 5.2 TB/s); 200 rows at lmax 16000 67 us, now 16 us.
-template <int T>
+template <int T, int PIECE>
 __global__ void __launch_bounds__(T) threej_rows_kernel(ThreejArgs a) {
     const long long p = blockIdx.x;
     const int l1 = a.l1[p], l2 = a.l2[p];
@@ -140,12 +137,12 @@ __global__ void __launch_bounds__(T) threej_rows_kernel(ThreejArgs a) {
     const bool nan = l1 < 0 || l2 < 0 || l1 > a.lmax_max || l2 > a.lmax_max;
     const int jmin = l1 > l2 ? l1 - l2 : l2 - l1;
     if (nan || min(l1, l2) < a.m) {           // a selection rule |m| <= l fails: zeros
-        each_piece<T>(row, 0, a.stride, a.piece, nan, [](int, int) {});
+        each_piece<T, PIECE>(row, 0, a.stride, nan, [](int, int) {});
         return;
     }
     const int n = l1 + l2 - jmin + 1;
     if (a.m == 0) {
-        each_piece<T>(row, n, a.stride, a.piece, false, [&](int lo, int hi) {
+        each_piece<T, PIECE>(row, n, a.stride, false, [&](int lo, int hi) {
             for (int i = lo + 2 * threadIdx.x; i < hi; i += 2 * T) {
                 const int P = (l1 + l2 + jmin + i) / 2;
                 const double r = sqrt(a.g[P - l1] * a.g[P - l2] * a.g[P - jmin - i] * a.h[P]);
@@ -164,7 +161,7 @@ __global__ void __launch_bounds__(T) threej_rows_kernel(ThreejArgs a) {
     const long long dd = (long long)l2 - l1;
     const double s1 = (double)((s + 1) * (s + 2)), d1 = (double)(dd * (dd + 1));
     const double mu = (double)(2LL * (l1 + 2) * (l2 + 2) - (s + 2) * (s + 3));
-    each_piece<T>(row, n, a.stride, a.piece, false, [&](int lo, int hi) {
+    each_piece<T, PIECE>(row, n, a.stride, false, [&](int lo, int hi) {
         for (int i0 = lo + threadIdx.x; i0 < hi; i0 += T * kThreejBatch) {
             double v[kThreejBatch];
 #pragma unroll
@@ -277,7 +274,6 @@ struct FamilyArgs {
     double* out;                 // [n_pairs][stride]
     long long stride;
     int lmax_max;
-    int piece;                   // entries per block
     int rot;                     // (x, y, z) = (l1, l2, l3) rotated left by rot
     int flip;                    // 1: times (-1)^L
 };
@@ -353,14 +349,14 @@ __device__ inline double family_symbol(const FamilyArgs& f, long long l1, long l
 }
 
 // The general kernel: rows whose l3 is not the column z.
-template <int AB, int T>
+template <int AB, int T, int PIECE>
 __global__ void __launch_bounds__(T) threej_family_kernel(FamilyArgs f) {
     const long long p = blockIdx.x;
     const int l1 = f.l1[p], l2 = f.l2[p];
     double* row = f.out + p * f.stride;
     const bool nan = l1 < 0 || l2 < 0 || l1 > f.lmax_max || l2 > f.lmax_max;
     const long long jmin = l1 > l2 ? l1 - l2 : l2 - l1;
-    each_piece<T>(row, nan ? 0 : (long long)l1 + l2 - jmin + 1, f.stride, f.piece, nan, [&](int lo, int hi) {
+    each_piece<T, PIECE>(row, nan ? 0 : (long long)l1 + l2 - jmin + 1, f.stride, nan, [&](int lo, int hi) {
         for (int i = lo + threadIdx.x; i < hi; i += T) {
             const double v = i < hi ? family_symbol<AB>(f, l1, l2, jmin + i) : 0.0;
             if (i < hi) row[i] = v;
@@ -387,7 +383,7 @@ __device__ inline unsigned __int128 mul_u32(unsigned __int128 v, unsigned c) {
 // What bounds it: about 150 instructions per symbol.  2000 rows of (2 2 -4) at lmax 6000
 // take 54 us, with the full 128-bit polynomials of both parities and two roots per
 // symbol 131 us; (1 1 -2) 43 us, before 78 us.
-template <int AB, int T>
+template <int AB, int T, int PIECE>
 __global__ void __launch_bounds__(T) threej_family_row_kernel(FamilyArgs f) {
     constexpr int a = AB / 3, b = AB % 3;
     const long long p = blockIdx.x;
@@ -395,7 +391,7 @@ __global__ void __launch_bounds__(T) threej_family_row_kernel(FamilyArgs f) {
     double* row = f.out + p * f.stride;
     const bool nan = l1 < 0 || l2 < 0 || l1 > f.lmax_max || l2 > f.lmax_max;
     if (nan || l1 < a || l2 < b) {
-        each_piece<T>(row, 0, f.stride, f.piece, nan, [](int, int) {});
+        each_piece<T, PIECE>(row, 0, f.stride, nan, [](int, int) {});
         return;
     }
     const int jmin = l1 > l2 ? l1 - l2 : l2 - l1, n = l1 + l2 - jmin + 1;
@@ -417,7 +413,7 @@ __global__ void __launch_bounds__(T) threej_family_row_kernel(FamilyArgs f) {
     for (int k = 0; k < a; ++k) dab *= (double)(A - k * (k + 1));
 #pragma unroll
     for (int k = 0; k < b; ++k) dab *= (double)(B - k * (k + 1));
-    each_piece<T>(row, n, f.stride, f.piece, false, [&](int lo, int hi) {
+    each_piece<T, PIECE>(row, n, f.stride, false, [&](int lo, int hi) {
         for (int i0 = lo + threadIdx.x; i0 < hi; i0 += T * kThreejBatch) {
             double v[kThreejBatch];
 #pragma unroll
@@ -460,20 +456,21 @@ hipError_t launch_threej_family(const couple_ctx* ctx, int rot, int flip, int a,
     f.lmax_max = ctx->lmax_max;
     f.rot = rot;
     f.flip = flip;
-    f.piece = row_piece(n_pairs, stride, kFamilyPastPiece);
-    const dim3 grid = piece_grid(n_pairs, stride, f.piece);
-    auto launch_threads = [&](auto ab, auto threads) {
-        constexpr int AB = decltype(ab)::value, T = decltype(threads)::value;
+    auto launch_form = [&](auto ab, auto threads, auto piece) {
+        constexpr int AB = decltype(ab)::value, T = decltype(threads)::value, PIECE = decltype(piece)::value;
+        const dim3 grid = piece_grid(n_pairs, stride, PIECE);
         if (rot == 0)
-            hipLaunchKernelGGL((threej_family_row_kernel<AB, T>), grid, dim3(T), 0, s, f);
+            hipLaunchKernelGGL((threej_family_row_kernel<AB, T, PIECE>), grid, dim3(T), 0, s, f);
         else
-            hipLaunchKernelGGL((threej_family_kernel<AB, T>), grid, dim3(T), 0, s, f);
+            hipLaunchKernelGGL((threej_family_kernel<AB, T, PIECE>), grid, dim3(T), 0, s, f);
     };
     auto launch = [&](auto ab) {
         if (stride <= kThreejShort)
-            launch_threads(ab, std::integral_constant<int, 64>());
+            launch_form(ab, std::integral_constant<int, 64>(), std::integral_constant<int, kThreejPiece>());
+        else if (past_cache(n_pairs, stride))
+            launch_form(ab, std::integral_constant<int, 256>(), std::integral_constant<int, kFamilyPastPiece>());
         else
-            launch_threads(ab, std::integral_constant<int, 256>());
+            launch_form(ab, std::integral_constant<int, 256>(), std::integral_constant<int, kThreejPiece>());
     };
     switch (3 * a + b) {
     case 0: launch(std::integral_constant<int, 0>()); break;
@@ -502,14 +499,16 @@ hipError_t launch_threej_rows(const couple_ctx* ctx, int m, int n_pairs, const i
     a.stride = stride;
     a.lmax_max = ctx->lmax_max;
     a.m = m;
-    a.piece = row_piece(n_pairs, stride, kThreejPastPiece);
-    const dim3 grid = piece_grid(n_pairs, stride, a.piece);
-    if (m == 0 && a.piece != kThreejPiece && stride >= kZeroRowsFrom && stride <= kZeroRowsTo)
+    const bool past = past_cache(n_pairs, stride);
+    if (m == 0 && past && stride >= kZeroRowsFrom && stride <= kZeroRowsTo)
         hipLaunchKernelGGL(threej_zero_rows_kernel, dim3((unsigned)n_pairs), dim3(256), kZeroRowsLds, s, a);
     else if (stride <= kThreejShort)
-        hipLaunchKernelGGL(threej_rows_kernel<64>, grid, dim3(64), 0, s, a);
+        hipLaunchKernelGGL((threej_rows_kernel<64, kThreejPiece>), piece_grid(n_pairs, stride, kThreejPiece), dim3(64), 0, s, a);
+    else if (past)
+        hipLaunchKernelGGL((threej_rows_kernel<256, kThreejPastPiece>), piece_grid(n_pairs, stride, kThreejPastPiece), dim3(256), 0,
+                           s, a);
     else
-        hipLaunchKernelGGL(threej_rows_kernel<256>, grid, dim3(256), 0, s, a);
+        hipLaunchKernelGGL((threej_rows_kernel<256, kThreejPiece>), piece_grid(n_pairs, stride, kThreejPiece), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
